@@ -288,13 +288,12 @@ rt_status rt_set_transport_path(rt_ctx *ctx, int path);
 /* Kernel arrangement of the chemistry that follows a separate transport
  * (rt_thermochem, and rt_step on the z-marching path; App. A); results are
  * the same bits on every path:
- *   RT_CHEM_AUTO      one pass on grids of 2,000,000 cells or more, two
- *                     passes on smaller ones (the faster of the two there)
+ *   RT_CHEM_AUTO      one pass (the faster of the two on every grid measured)
  *   RT_CHEM_TWO_PASS  a head pass of head_attempts attempts per cell in
  *                     lockstep, then the queued cells in a persistent tail
  *   RT_CHEM_ONE_PASS  one persistent pass whose lanes take the next cell as
  *                     soon as theirs has filled dt_RT, cells whose previous
- *                     pass took many attempts first
+ *                     pass took many attempts first, warm and cold gas apart
  * The per-cell transport path's rt_step always runs its fused head pass and
  * the tail. */
 enum { RT_CHEM_AUTO = 0, RT_CHEM_TWO_PASS = 1, RT_CHEM_ONE_PASS = 2 };

@@ -2,12 +2,17 @@
 import os
 import subprocess
 import sys
+from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "librtm1.so")
-SOURCES = ["rt_api.hip", "rt_kernels.hip", "rt_transport.hip", "rt_batch.hip", "rt_adjoint.hip"]
+# (object, source, defines); the chemistry kernels build once per radiation
+# type and method variant
+UNITS = [(f"rt_chem_{r}{v}", "rt_chem.hip", [f"-DRT_CHEM_R={t}", f"-DRT_CHEM_V={v}"])
+         for r, t in (("f", "float"), ("d", "double")) for v in range(4)]
+UNITS += [(n, n + ".hip", []) for n in ("rt_batch", "rt_transport", "rt_adjoint", "rt_kernels", "rt_api")]
 
 HIPCC_FLAGS = [
     "-O3", "-std=c++17", "-fPIC", "-shared", "--offload-arch=gfx950",
@@ -17,26 +22,22 @@ HIPCC_FLAGS = [
 ]
 
 
-def build(verbose: bool = False, jobs: int = 3) -> str:
+def build(verbose: bool = False, jobs: int = 0) -> str:
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-    objs = []
-    procs = []
-    for src in SOURCES:
-        obj = os.path.join(CSRC, src.replace(".hip", ".o"))
-        cmd = [hipcc, *[f for f in HIPCC_FLAGS if f != "-shared"], "-c", os.path.join(CSRC, src),
+    jobs = jobs or min(8, os.cpu_count() or 1)
+
+    def compile_unit(unit):
+        name, src, defines = unit
+        obj = os.path.join(CSRC, name + ".o")
+        cmd = [hipcc, *[f for f in HIPCC_FLAGS if f != "-shared"], *defines, "-c", os.path.join(CSRC, src),
                "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-o", obj]
         if verbose:
             print(" ".join(cmd), flush=True)
-        procs.append(subprocess.Popen(cmd))
-        objs.append(obj)
-        if len(procs) >= jobs:
-            for p in procs:
-                if p.wait() != 0:
-                    raise RuntimeError("hipcc failed")
-            procs = []
-    for p in procs:
-        if p.wait() != 0:
-            raise RuntimeError("hipcc failed")
+        subprocess.run(cmd, check=True)
+        return obj
+
+    with ThreadPoolExecutor(jobs) as pool:
+        objs = list(pool.map(compile_unit, UNITS))
     cmd = [hipcc, "-shared", "-fPIC", "--offload-arch=gfx950", *objs, "-o", LIB + ".tmp"]
     if verbose:
         print(" ".join(cmd), flush=True)

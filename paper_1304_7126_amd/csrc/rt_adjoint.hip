@@ -143,6 +143,11 @@ template <>
 __device__ __forceinline__ Dual cst<Dual>(double v) { return dconst(v); }
 
 // ---------------------------------------------- App. E rates, dual numbers
+// ln of the hydrogen fits' threshold temperature and break points
+constexpr double LN_TL_HI = 12.662275226919286;  // ln 315614
+constexpr double LN_2p74 = 1.007957920399979;
+constexpr double LN_2p25 = 0.8109302162163288;
+
 // The hydrogen terms of the case-B rate set with their d/dT, as functions
 // of a dual temperature (so that d/dT itself is differentiated too).
 template <class D>
@@ -300,7 +305,8 @@ __global__ __launch_bounds__(256) void k_chem_record(const KChem *__restrict__ k
     CS s;
     s.N[0] = (double)N[i];
     s.N[1] = s.N[2] = 0.0;
-    s.fs[1] = s.fs[2] = 1.0;
+    s.fs[1] = 1.0;
+    s.fs[2] = 1.0;
     const double F0[3] = {(double)F[i], (double)F[nc + i], (double)F[2 * nc + i]};
     s.x = xHII[i];
     s.y2 = 0.0;
@@ -316,7 +322,7 @@ __global__ __launch_bounds__(256) void k_chem_record(const KChem *__restrict__ k
         const double e5 = k.isothermal ? cc.Tiso : s.Tmu;
         const double h = s.h >= s.rem * (1.0 - 1e-10) ? s.rem : s.h;  // the length chem_attempt takes
         const int acc0 = s.acc;
-        done = chem_attempt<CM, 0, false>(k, cc, s, fl);  // one attempt per call: h above is its length
+        done = chem_attempt<CM, 0, false, false>(k, k.rates, nullptr, cc, s, fl);  // one attempt per call: h above is its length
         if (s.acc != acc0) {
             if (fits && n < cnt) {
                 double *e = tr + TV * n;

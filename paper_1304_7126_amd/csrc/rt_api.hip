@@ -11,6 +11,7 @@
 #include <vector>
 
 #include "rt_internal.h"
+#include "rt_rates.h"
 #include "rtm1.h"
 
 using namespace rtm1;
@@ -22,6 +23,7 @@ struct rt_ctx {
     rt_params params;
     KChem kchem;
     KChem *dkchem = nullptr;   // device copy read by the chemistry kernels
+    double *drates = nullptr;  // rate table kchem points to
     bool fp32 = false;
     int nf = 101, nth = 101;
     std::vector<double> hll_host;
@@ -224,6 +226,28 @@ static void build_hll(int nf, int nth, std::vector<double> &tab)
         }
     }
 }
+
+// ---------------------------------------------------------------------------
+// Rate tables (rt_rates.h): built once per process and case (7 ms), copied
+// to every context's device.
+// ---------------------------------------------------------------------------
+namespace rtm1 {
+hipError_t upload_rate_table(bool otsa, double **out)
+{
+    static std::mutex mu;
+    static std::vector<double> host[2];  // case B, case A
+    std::vector<double> &t = host[otsa ? 0 : 1];
+    const size_t n = otsa ? RTX::len_b : RTX::len_a;
+    std::lock_guard<std::mutex> lk(mu);
+    if (t.empty()) {
+        t.resize(n);
+        build_rate_table(!otsa, t.data());
+    }
+    hipError_t e = hipMalloc((void **)out, n * sizeof(double));
+    if (e == hipSuccess) e = hipMemcpy(*out, t.data(), n * sizeof(double), hipMemcpyHostToDevice);
+    return e;
+}
+}  // namespace rtm1
 
 // ---------------------------------------------------------------------------
 // Group attributes (Sec. 2, eqs. csn_multi, egy_multi, cse_multi) of a
@@ -461,6 +485,8 @@ extern "C" rt_status rt_init(const rt_grid *grid, const rt_groups *groups, const
     if (e == hipSuccess) e = hipMalloc((void **)&c->dstats, sizeof(DevStats));
     if (e == hipSuccess) e = hipMemset(c->dstats, 0, sizeof(DevStats));
     if (e == hipSuccess) e = hipMalloc((void **)&c->dred, sizeof(RedOut));
+    if (e == hipSuccess) e = upload_rate_table(params->otsa != 0, &c->drates);
+    k.rates = c->drates;
     if (e == hipSuccess) e = hipMalloc((void **)&c->dkchem, sizeof(KChem));
     if (e == hipSuccess) e = hipMemcpy(c->dkchem, &c->kchem, sizeof(KChem), hipMemcpyHostToDevice);
     if (e != hipSuccess) {
@@ -685,6 +711,7 @@ extern "C" rt_status rt_set_expansion(rt_ctx *c, double a)
     RT_HIP(c, hipStreamSynchronize(c->stream));
     c->a_cosmo = a;
     c->kchem.a_exp = a;
+    kchem_derive(c->kchem);
     RT_HIP(c, hipMemcpy(c->dkchem, &c->kchem, sizeof(KChem), hipMemcpyHostToDevice));
     return RT_OK;
 }
@@ -792,23 +819,13 @@ static SmoothArgs smooth_args(const rt_ctx *c, int pre_set, bool injected)
     return a;
 }
 
-// One pass or two for the chemistry after a separate transport.  Measured
-// on the lognormal workload (mixed precision, n/256 x 200 sources, steps
-// 1-40, ms per step, one pass / two passes): 96^3 1.00 / 0.85, 128^3 1.30 /
-// 1.19, 160^3 1.76 / 1.90, 192^3 2.16 / 2.51, 224^3 3.17 / 3.97; at 128^3
-// with more I-front cells the one pass is ahead (FP64, 50 sources, 200
-// steps: 1.18 / 1.24; the shadow test: 0.94 / 1.07).  On small grids the
-// lockstep head pass, with many more waves in flight, hides the latency of
-// taking cells better than the persistent lanes do; long chains favour the
-// one pass, which starts them first.
-constexpr size_t CHEM_ONE_PASS_MIN_CELLS = 2000000;
-
-static bool use_one_pass(const rt_ctx *c)
-{
-    if (c->chem_path == RT_CHEM_ONE_PASS) return true;
-    if (c->chem_path == RT_CHEM_TWO_PASS) return false;
-    return c->grid.ncell >= CHEM_ONE_PASS_MIN_CELLS;
-}
+// One pass or two for the chemistry after a separate transport: one pass at
+// every size.  Measured with the rate table (us per step, one pass / two
+// passes): 16^3 89 / 103, isothermal 32^3 66 / 94, 97 x 61 x 45 275 / 307,
+// 64^3 354 / 400 (before it the two passes were ahead below 2,000,000
+// cells: the persistent lanes' longer chains of instructions hid less of
+// their latency there).
+static bool use_one_pass(const rt_ctx *c) { return c->chem_path != RT_CHEM_TWO_PASS; }
 
 static rt_status do_chem(rt_ctx *c, double dt)
 {
@@ -1246,6 +1263,7 @@ extern "C" void rt_free(rt_ctx *c)
     if (c->dstats) (void)hipFree(c->dstats);
     if (c->dred) (void)hipFree(c->dred);
     if (c->dkchem) (void)hipFree(c->dkchem);
+    if (c->drates) (void)hipFree(c->drates);
     for (auto &p : c->pend) {
         (void)hipEventDestroy(p.a);
         (void)hipEventDestroy(p.b);

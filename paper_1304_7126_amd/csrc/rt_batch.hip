@@ -164,7 +164,7 @@ __global__ void k_bzero(unsigned *p) { if (threadIdx.x < 3) p[threadIdx.x] = 0u;
 template <typename R, int M, int FLUX>
 __device__ __forceinline__ void head_chunk(const BoxDev &b, uint32_t box, uint32_t start, int src, double dt, R c,
                                            const R *__restrict__ tab, int nf, int nth, const BQueue &q,
-                                           unsigned stride, int K, unsigned long long &a_acc,
+                                           unsigned stride, int K, const double *rx, const double *rt, unsigned long long &a_acc,
                                            unsigned long long &a_att, unsigned long long &a_max, unsigned &fl)
 {
     const KChem &k = *b.kchem;
@@ -207,7 +207,7 @@ __device__ __forceinline__ void head_chunk(const BoxDev &b, uint32_t box, uint32
         cc = make_cc(k, b.nH[i], b.T[i]);
         if (chem_init<CM>(k, dt, cc.Tiso, fin, s)) {
             done = false;
-            for (int a = 0; a < K && !done; ++a) done = chem_attempt<CM>(k, cc, s, fl);
+            for (int a = 0; a < K && !done; ++a) done = chem_attempt<CM>(k, rx, rt, cc, s, fl);
         } else {
             fl |= 2u;
         }
@@ -232,7 +232,7 @@ __device__ __forceinline__ void head_chunk(const BoxDev &b, uint32_t box, uint32
         }
     }
     if (want && !queued) {
-        while (!done) done = chem_attempt<CM>(k, cc, s, fl);
+        while (!done) done = chem_attempt<CM>(k, rx, rt, cc, s, fl);
     }
     if (valid && !queued) {
         const double T = chem_finish<CM>(k, cc, s, fl);
@@ -274,12 +274,14 @@ __device__ __forceinline__ void bblock_stats(DevStats *st, unsigned long long ac
 }
 
 template <typename R, int FLUX>
-__global__ __launch_bounds__(256) void k_bhead(const BoxDev *__restrict__ boxes, const Chunk *__restrict__ chunks,
+__global__ __launch_bounds__(256) void k_bhead(const BoxDev *__restrict__ boxes, const double *__restrict__ rx, const Chunk *__restrict__ chunks,
                                                unsigned nchunks, BQueue q, unsigned stride, int K, int src,
                                                double dt, R c, const R *__restrict__ tab, int nf, int nth,
                                                DevStats *__restrict__ st)
 {
     const int lane = (int)(threadIdx.x & 63u);
+    __shared__ double rt[rate_table_len<0>()];
+    rate_table_to_lds<0>(rx, rt);
     unsigned long long a_acc = 0, a_att = 0, a_max = 0;
     unsigned fl = 0;
     while (true) {
@@ -290,11 +292,11 @@ __global__ __launch_bounds__(256) void k_bhead(const BoxDev *__restrict__ boxes,
         const Chunk ch = chunks[ci];
         const BoxDev &b = boxes[ch.box];
         if (b.M == 1)
-            head_chunk<R, 1, FLUX>(b, ch.box, ch.start, src, dt, c, tab, nf, nth, q, stride, K, a_acc, a_att, a_max, fl);
+            head_chunk<R, 1, FLUX>(b, ch.box, ch.start, src, dt, c, tab, nf, nth, q, stride, K, rx, rt, a_acc, a_att, a_max, fl);
         else if (b.M == 2)
-            head_chunk<R, 2, FLUX>(b, ch.box, ch.start, src, dt, c, tab, nf, nth, q, stride, K, a_acc, a_att, a_max, fl);
+            head_chunk<R, 2, FLUX>(b, ch.box, ch.start, src, dt, c, tab, nf, nth, q, stride, K, rx, rt, a_acc, a_att, a_max, fl);
         else
-            head_chunk<R, 3, FLUX>(b, ch.box, ch.start, src, dt, c, tab, nf, nth, q, stride, K, a_acc, a_att, a_max, fl);
+            head_chunk<R, 3, FLUX>(b, ch.box, ch.start, src, dt, c, tab, nf, nth, q, stride, K, rx, rt, a_acc, a_att, a_max, fl);
     }
     bblock_stats(st, a_acc, a_att, a_max, fl);
 }
@@ -302,10 +304,12 @@ __global__ __launch_bounds__(256) void k_bhead(const BoxDev *__restrict__ boxes,
 // Tail: lanes hold cells of any box (the attempt runs with three groups, as
 // in every chemistry kernel).
 template <typename R>
-__global__ __launch_bounds__(256) void k_btail(const BoxDev *__restrict__ boxes, BQueue q, unsigned stride, int dst,
+__global__ __launch_bounds__(256) void k_btail(const BoxDev *__restrict__ boxes, const double *__restrict__ rx, BQueue q, unsigned stride, int dst,
                                                double dt, DevStats *__restrict__ st)
 {
     const int lane = (int)(threadIdx.x & 63u);
+    __shared__ double rt[rate_table_len<0>()];
+    rate_table_to_lds<0>(rx, rt);
     const unsigned n = min(q.ctr[1], q.cap);
     CS s;
     R fpre[9];  // the cell's transported flux, loaded with the cell (used when it is written)
@@ -354,7 +358,7 @@ __global__ __launch_bounds__(256) void k_btail(const BoxDev *__restrict__ boxes,
         if (!__any(active)) break;
         if (active) {
             const KChem &k = *boxes[box].kchem;
-            if (chem_attempt<CM>(k, cc, s, fl)) {
+            if (chem_attempt<CM>(k, rx, rt, cc, s, fl)) {
                 const double T = chem_finish<CM>(k, cc, s, fl);
                 bstore<R>(boxes[box], dst, cell, s, T, fpre);
                 a_acc += (unsigned long long)s.acc;
@@ -384,6 +388,7 @@ struct rt_batch {
     std::vector<double> dx;
     BoxDev *dboxes = nullptr;
     KChem *dkchem = nullptr;
+    double *drates = nullptr;  // rate table the boxes' KChem point to
     Chunk *dchunks = nullptr;
     unsigned nchunks = 0;
     void *hll = nullptr;
@@ -553,6 +558,8 @@ extern "C" rt_status rt_batch_init(int nbox, const rt_grid *grids, const rt_grou
     if (e == hipSuccess) e = hipGetDevice(&dev);
     if (e == hipSuccess) e = hipDeviceGetAttribute(&b->ncu, hipDeviceAttributeMultiprocessorCount, dev);
     if (e == hipSuccess) e = hipMalloc((void **)&b->dboxes, nbox * sizeof(BoxDev));
+    if (e == hipSuccess) e = upload_rate_table(true, &b->drates);
+    for (KChem &k : b->kchem) k.rates = b->drates;
     if (e == hipSuccess) e = hipMalloc((void **)&b->dkchem, nbox * sizeof(KChem));
     if (e == hipSuccess) e = hipMemcpy(b->dkchem, b->kchem.data(), nbox * sizeof(KChem), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMalloc((void **)&b->dchunks, chunks.size() * sizeof(Chunk));
@@ -714,15 +721,15 @@ static rt_status enqueue_step(rt_batch *b, double dt, int src)
     const unsigned tb = (unsigned)b->tail_blocks;
     if (b->fp32) {
         auto hk = b->flux ? k_bhead<float, 1> : k_bhead<float, 0>;
-        hipLaunchKernelGGL(hk, dim3(hb), dim3(256), 0, s, b->dboxes, b->dchunks, b->nchunks, q, b->qcap_max,
+        hipLaunchKernelGGL(hk, dim3(hb), dim3(256), 0, s, b->dboxes, b->drates, b->dchunks, b->nchunks, q, b->qcap_max,
                            b->head_attempts, src, dt, (float)b->c_r, (const float *)b->hll, b->nf, b->nth, b->dstats);
-        hipLaunchKernelGGL(k_btail<float>, dim3(tb), dim3(256), 0, s, b->dboxes, q, b->qcap_max, 1 - src, dt,
+        hipLaunchKernelGGL(k_btail<float>, dim3(tb), dim3(256), 0, s, b->dboxes, b->drates, q, b->qcap_max, 1 - src, dt,
                            b->dstats);
     } else {
         auto hk = b->flux ? k_bhead<double, 1> : k_bhead<double, 0>;
-        hipLaunchKernelGGL(hk, dim3(hb), dim3(256), 0, s, b->dboxes, b->dchunks, b->nchunks, q, b->qcap_max,
+        hipLaunchKernelGGL(hk, dim3(hb), dim3(256), 0, s, b->dboxes, b->drates, b->dchunks, b->nchunks, q, b->qcap_max,
                            b->head_attempts, src, dt, b->c_r, (const double *)b->hll, b->nf, b->nth, b->dstats);
-        hipLaunchKernelGGL(k_btail<double>, dim3(tb), dim3(256), 0, s, b->dboxes, q, b->qcap_max, 1 - src, dt,
+        hipLaunchKernelGGL(k_btail<double>, dim3(tb), dim3(256), 0, s, b->dboxes, b->drates, q, b->qcap_max, 1 - src, dt,
                            b->dstats);
     }
     BT_HIP(b, hipGetLastError());
@@ -822,6 +829,7 @@ extern "C" void rt_batch_free(rt_batch *b)
     drop_graphs(b);
     if (b->dboxes) (void)hipFree(b->dboxes);
     if (b->dkchem) (void)hipFree(b->dkchem);
+    if (b->drates) (void)hipFree(b->drates);
     if (b->dchunks) (void)hipFree(b->dchunks);
     if (b->dsrc) (void)hipFree(b->dsrc);
     if (b->dstats) (void)hipFree(b->dstats);

@@ -202,10 +202,35 @@ __device__ __forceinline__ U4<R> transport_cell(const Nbr &nb, uint32_t i, size_
     return o;
 }
 
+// Fixed-order block sum of the per-thread values v[0..5] (transported N and
+// outward boundary flux per group) into part[6 * blockIdx.x + q].  Called by
+// every thread of a 256-thread block.
+__device__ __forceinline__ void block_acct(double *part, const double v[6])
+{
+    __shared__ double sh[6][ACCT_THREADS];
+    const int t = threadIdx.x;
+#pragma unroll
+    for (int q = 0; q < 6; ++q) sh[q][t] = v[q];
+    __syncthreads();
+    for (int o = ACCT_THREADS / 2; o > 0; o >>= 1) {
+        if (t < o) {
+#pragma unroll
+            for (int q = 0; q < 6; ++q) sh[q][t] += sh[q][t + o];
+        }
+        __syncthreads();
+    }
+    if (t < 6) part[(size_t)6 * blockIdx.x + t] = sh[t][0];
+}
+
 // --------------------------------------------------------- thermochemistry
+// 1/mu and mu, the mean particle mass in units of m_H
+__device__ __forceinline__ double imu_of(const KChem &k, double x, double y2, double y3)
+{
+    return k.X * (1.0 + x) + 0.25 * k.Y * (1.0 + y2 + 2.0 * y3);
+}
 __device__ __forceinline__ double mu_of(const KChem &k, double x, double y2, double y3)
 {
-    return rcp_pos(k.X * (1.0 + x) + 0.25 * k.Y * (1.0 + y2 + 2.0 * y3));
+    return rcp_pos(imu_of(k, x, y2, y3));
 }
 
 // |a - b| > f b for b > 0: the relative-change test of App. A without a division
@@ -216,6 +241,7 @@ __device__ __forceinline__ bool rel_above(double a, double b, double f) { return
 // substep, so the state carries that product (fs) and the flux itself stays
 // in the destination arrays until the cell has finished.
 struct CS {
+    static constexpr bool smooth = false;
     double N[3], fs[3];
     double x, y2, y3, Tmu;
     double rem, h;  // time left in dt_RT, length of the next substep
@@ -230,8 +256,11 @@ struct CS {
 // absorption factors r_k = 1/(1 + h_k D_k) it is fs F^t + fb (F' - F^t)/dt_RT
 // with fs = prod r_k and fb <- (fb + h_k) r_k; the state carries fb.
 struct CSR : CS {
+    static constexpr bool smooth = true;
     double Nr[3], fb[3];
 };
+template <int V>
+using ChemState = std::conditional_t<(V & 1) != 0, CSR, CS>;
 
 // Every chemistry kernel runs the attempt with three groups; groups a grid
 // does not have carry zero photons and zero cross sections, which leaves
@@ -251,7 +280,7 @@ __device__ __forceinline__ CC make_cc(const KChem &k, double nH, double T)
 {
     CC c;
     c.nH = nH;
-    c.nHe = nH * k.Y / (4.0 * k.X);
+    c.nHe = nH * k.HeH;
     c.K = k.Kfac / nH;
     c.Tiso = T;
     return c;
@@ -279,7 +308,7 @@ __device__ __forceinline__ bool chem_init(const KChem &k, double dt, double T, b
             s.fb[g] = 0.0;
         }
     }
-    s.Tmu = T / mu_of(k, s.x, s.y2, s.y3);
+    s.Tmu = T * imu_of(k, s.x, s.y2, s.y3);
     s.rem = ok ? dt : 0.0;
     s.h = dt;
     s.acc = 0;
@@ -287,6 +316,35 @@ __device__ __forceinline__ bool chem_init(const KChem &k, double dt, double T, b
     return ok;
 }
 
+// The rate table in LDS for a workgroup of persistent lanes (all its threads
+// call this): 75 KB, without OTSA 113 KB.
+template <int V>
+constexpr int rate_table_len() { return (V & V_CASE_A) ? RTL::len_a : RTL::len_b; }
+__device__ __forceinline__ void copy_columns(gptr src, double *dst, int rows, int sstride, int dstride)
+{
+    // pairs of columns
+    for (int j = threadIdx.x; j < rows * (dstride / 2); j += blockDim.x) {
+        const int r = j / (dstride / 2), c = j - r * (dstride / 2);
+        dst[r * dstride + 2 * c] = src[r * sstride + 2 * c];
+        dst[r * dstride + 2 * c + 1] = src[r * sstride + 2 * c + 1];
+    }
+}
+template <int V>
+__device__ __forceinline__ void rate_table_to_lds(const double *__restrict__ xx, double *l)
+{
+    const gptr x = (gptr)xx;
+    constexpr int o0 = RT_LOFF / RT_SUB;
+    copy_columns(x + RTX::A + RT_LOFF, l + RTL::A, RT_COEF, RT_XNI, RT_LNI);
+    copy_columns(x + RTX::E + RT_LOFF, l + RTL::E, RT_COEF, RT_XNI, RT_LNI);
+    copy_columns(x + RTX::P, l + RTL::P, 1, 0, 2 * RT_COEF * RT_SUB);  // P and Q
+    copy_columns(x + RTX::PO + o0, l + RTL::PO, 2, RT_XNOCT, RT_LNOCT);
+    if constexpr ((V & V_CASE_A) != 0) {
+        copy_columns(x + RTX::DA + RT_LOFF, l + RTL::DA, RT_COEF, RT_XNI, RT_LNI);
+        copy_columns(x + RTX::PB, l + RTL::PB, 1, 0, RT_COEF * RT_SUB);
+        copy_columns(x + RTX::PBO + o0, l + RTL::PBO, 1, 0, RT_LNOCT);
+    }
+    __syncthreads();
+}
 // One attempt of a substep of length h (App. A tasks 1-5).  On a failed
 // 10% check the state is unchanged and h is halved; on success the state
 // advances by h, and the next h doubles when every relative change was
@@ -296,45 +354,54 @@ __device__ __forceinline__ bool chem_init(const KChem &k, double dt, double T, b
 // with the halved h inside the call before the gas stages run: each still
 // counts as an attempt, and the sequence of attempts is the same, but a
 // lane that would sit out the rest of a failed attempt goes on at once.
-template <int M, int V = 0, bool RETRY = true, class St>
-__device__ __forceinline__ bool chem_attempt(const KChem &k, const CC &cc, St &s, unsigned &flags)
+// The rates come from the table rx in global memory or (LDS) its copy rl in
+// LDS; rx is the same for every lane.
+template <int M, int V = 0, bool RETRY = true, bool LDS = true, class St>
+__device__ __forceinline__ bool chem_attempt(const KChem &k, const double *rx, const double *rl, const CC &cc, St &s, unsigned &flags)
 {
     constexpr bool SM = (V & V_SMOOTH) != 0;
     constexpr bool CA = (V & V_CASE_A) != 0;
-    if (s.att >= k.max_att) {
-        flags |= 1u;
-        return true;
-    }
-    ++s.att;
+    const Rates<CA, LDS> rates(rx, rl);
     const bool iso = k.isothermal != 0;
     const double nH = cc.nH, nHe = cc.nHe, K = cc.K;
-    double h = s.h;
-    if (h >= s.rem * (1.0 - 1e-10)) h = s.rem;
     const double x = s.x, y2 = s.y2, y3 = s.y3, Tmu = s.Tmu;
-    bool small = true;  // every relative change below 5%
     // ---- photons: semi-implicit absorption with backward abundances
     const double nHI = (1.0 - x) * nH;
     const double nHeI = (1.0 - y2 - y3) * nHe;
     const double nHeII = y2 * nHe;
     const double nHII = x * nH;
     const double nHeIII = y3 * nHe;
-    double Nn[M], rd[M], D[M];
+    double Nn[M] = {}, rd[M] = {}, D[M];
     // without OTSA: photons of recombinations straight to the ground state,
     // (alpha_A - alpha_B) n_j n_e with the state at the start of the
     // substep, into the group that holds species j's threshold (eq. cool_N_cr)
     double Crec[M];
     if constexpr (CA) {
-        const Tq qc = make_Tq(iso ? cc.Tiso : Tmu * mu_of(k, x, y2, y3));
+        const double Tc = iso ? cc.Tiso : Tmu * mu_of(k, x, y2, y3);
         const double ne = nHII + (y2 + 2.0 * y3) * nHe;
-        const double em0 = (alphaA_HII(qc).v - alphaB_HII(qc).v) * nHII * ne;
-        const double em1 = (alphaA_HeII(qc).v - alphaB_HeII(qc).v) * nHeII * ne;
-        const double em2 = (alphaA_HeIII(qc).v - alphaB_HeIII(qc).v) * nHeIII * ne;
+        double ex[3];
+        rates.excess(Tc, ex);
+        const double em0 = ex[0] * nHII * ne;
+        const double em1 = ex[1] * nHeII * ne;
+        const double em2 = ex[2] * nHeIII * ne;
 #pragma unroll
         for (int g = 0; g < M; ++g) Crec[g] = k.brec[g][0] * em0 + k.brec[g][1] * em1 + k.brec[g][2] * em2;
     }
 #pragma unroll
     for (int g = 0; g < M; ++g) D[g] = k.csN[g][0] * nHI + k.csN[g][1] * nHeI + k.csN[g][2] * nHeII;
+    double h = 0.0;
+    bool small = true;   // every relative change below 5%
+    bool live = false;   // the photon check passed
+    bool capped = false;
     for (;;) {
+        capped = s.att >= k.max_att32;
+        if (capped) {
+            flags |= 1u;
+            break;
+        }
+        ++s.att;
+        h = s.h >= s.rem * (1.0 - 1e-10) ? s.rem : s.h;
+        small = true;
         bool fail = false;
         if constexpr (M == 3) {
             // the three absorption factors 1/(1 + h D_g) from one division
@@ -364,25 +431,21 @@ __device__ __forceinline__ bool chem_attempt(const KChem &k, const CC &cc, St &s
                 small &= fabs(Nn[g] - s.N[g]) < 0.05 * s.N[g];
             }
         }
-        if (!fail) break;
+        live = !fail;
+        if (live) break;
         s.h = 0.5 * h;
-        if (!RETRY) return false;
-        // the next attempt, from its start
-        if (s.att >= k.max_att) {
-            flags |= 1u;
-            return true;
-        }
-        ++s.att;
-        h = s.h;
-        if (h >= s.rem * (1.0 - 1e-10)) h = s.rem;
-        small = true;
+        if (!RETRY) break;
     }
+    // From here every lane runs every stage, and ok says whether its checks
+    // have held: the stages of a lane that failed one cost nothing while
+    // others go on, and early exits would make the compiler copy the whole
+    // state at each.
+    bool ok = live;
     const double mu0 = mu_of(k, x, y2, y3);
     const double ne0 = nHII + (y2 + 2.0 * y3) * nHe;
     // ---- thermal update in T_mu = T/mu
     double Tmun = Tmu;
     if (!iso) {
-        const Tq q0 = make_Tq(Tmu * mu0);
         double H = 0.0;
         {
             const double nj[3] = {nHI, nHeI, nHeII};
@@ -395,20 +458,14 @@ __device__ __forceinline__ bool chem_attempt(const KChem &k, const CC &cc, St &s
             }
         }
         double L, dL;
-        cooling<CA>(q0, k.a_exp, ne0, nHI, nHII, nHeI, nHeII, nHeIII, L, dL);
+        cooling(rates, Tmu * mu0, k.Tcmb, k.compton, ne0, nHI, nHII, nHeI, nHeII, nHeIII, L, dL);
         const double Lam = H - L;
         const double Lamp = -mu0 * dL;
         const double den = 1.0 - Lamp * K * h;
-        if (!(den > 0.0)) {
-            s.h = 0.5 * h;
-            return false;
-        }
         Tmun = Tmu + Lam * K * h / den;
-        if (rel_above(Tmun, Tmu, 0.1) || fabs(K * Lam * h) > 0.1 * Tmu) {
-            s.h = 0.5 * h;
-            return false;
-        }
-        small &= fabs(Tmun - Tmu) < 0.05 * Tmu;
+        ok = ok && den > 0.0 && !rel_above(Tmun, Tmu, 0.1) && !(fabs(K * Lam * h) > 0.1 * Tmu);
+        small = small && fabs(Tmun - Tmu) < 0.05 * Tmu;
+        Tmun = ok ? Tmun : Tmu;  // (keeps a failed lane's temperatures ordinary)
     }
     // ---- hydrogen: semi-implicit in x_HII
     double GHI = 0.0, GHeI = 0.0, GHeII = 0.0;
@@ -418,9 +475,10 @@ __device__ __forceinline__ bool chem_attempt(const KChem &k, const CC &cc, St &s
         GHeI += k.csN[g][1] * Nn[g];
         GHeII += k.csN[g][2] * Nn[g];
     }
-    const Tq q1 = make_Tq(iso ? cc.Tiso : Tmun * mu0);
-    const vd bH = beta_HI(q1);
-    const vd aH = alpha_HII<CA>(q1);
+    const double T1 = iso ? cc.Tiso : Tmun * mu0;
+    const vd aH = rates.alpha_HII(T1);
+    vd bH{0.0, 0.0};
+    if (!(T1 <= T_COLD_HI)) bH = beta_HI(rates.expc(), make_Tq(T1));
     const double Cr = bH.v * ne0 + GHI;
     const double Dr = aH.v * ne0;
     double dC, dD;
@@ -434,60 +492,64 @@ __device__ __forceinline__ bool chem_attempt(const KChem &k, const CC &cc, St &s
     }
     const double J = dC - (Cr + Dr) - x * (dC + dD);
     const double denx = 1.0 - J * h;
-    if (!(denx > 0.0)) {
-        s.h = 0.5 * h;
-        return false;
-    }
     const double rate = Cr - x * (Cr + Dr);
     double xn = x + h * rate / denx;
     xn = xn < k.x_min ? k.x_min : (xn > 1.0 ? 1.0 : xn);
-    if (rel_above(xn, x, 0.1) || fabs(rate) * h > 0.1 * x) {
-        s.h = 0.5 * h;
-        return false;
-    }
-    small &= fabs(xn - x) < 0.05 * x;
+    ok = ok && denx > 0.0 && !rel_above(xn, x, 0.1) && !(fabs(rate) * h > 0.1 * x);
+    small = small && fabs(xn - x) < 0.05 * x;
     // ---- helium: HeI, HeII, HeIII in order, then He conservation
     double y2n = y2, y3n = y3;
-    if (nHe > 0.0) {
+    if (k.Y > 0.0) {
         const double ne1 = xn * nH + (y2 + 2.0 * y3) * nHe;
-        const Tq q2 = make_Tq(iso ? cc.Tiso : Tmun * mu_of(k, xn, y2, y3));
-        const vd bHe1 = beta_HeI(q2), aHe2 = alpha_HeII<CA>(q2), bHe2 = beta_HeII(q2), aHe3 = alpha_HeIII<CA>(q2);
+        const double T2 = iso ? cc.Tiso : Tmun * mu_of(k, xn, y2, y3);
+        double aHe2, aHe3, bHe1 = 0.0, bHe2 = 0.0;
+        rates.alpha_He(T2, aHe2, aHe3);
+        if (!(T2 <= T_COLD_HEI)) {
+            const Tq q2 = make_Tq(T2);
+            const sptr ec = rates.expc();
+            bHe1 = beta_HeI(ec, q2).v;
+            bHe2 = beta_HeII(ec, q2).v;
+        }
         const double y1 = 1.0 - y2 - y3;
-        const double y1n = div_pos(y1 + y2 * aHe2.v * ne1 * h, 1.0 + (bHe1.v * ne1 + GHeI) * h);
-        y2n = div_pos(y2 + (y1n * (bHe1.v * ne1 + GHeI) + y3 * aHe3.v * ne1) * h,
-                      1.0 + ((bHe2.v + aHe2.v) * ne1 + GHeII) * h);
+        const double y1n = div_pos(y1 + y2 * aHe2 * ne1 * h, 1.0 + (bHe1 * ne1 + GHeI) * h);
+        y2n = div_pos(y2 + (y1n * (bHe1 * ne1 + GHeI) + y3 * aHe3 * ne1) * h,
+                      1.0 + ((bHe2 + aHe2) * ne1 + GHeII) * h);
         const double ne2 = xn * nH + (y2n + 2.0 * y3) * nHe;
-        const Tq q3 = make_Tq(iso ? cc.Tiso : Tmun * mu_of(k, xn, y2n, y3));
-        const vd bHe2b = beta_HeII(q3), aHe3b = alpha_HeIII<CA>(q3);
-        y3n = div_pos(y3 + y2n * (bHe2b.v * ne2 + GHeII) * h, 1.0 + aHe3b.v * ne2 * h);
+        const double T3 = iso ? cc.Tiso : Tmun * mu_of(k, xn, y2n, y3);
+        const double aHe3b = rates.alpha_HeIII(T3);
+        double bHe2b = 0.0;
+        if (!(T3 <= T_COLD_HEII)) bHe2b = beta_HeII(rates.expc(), make_Tq(T3)).v;
+        y3n = div_pos(y3 + y2n * (bHe2b * ne2 + GHeII) * h, 1.0 + aHe3b * ne2 * h);
         const double S = y1n + y2n + y3n;
         if (!(y1n >= y2n && y1n >= y3n)) {
             if (y2n >= y3n) y2n -= (S - 1.0);
             else y3n -= (S - 1.0);
         }
+        // no helium in an empty cell
+        y2n = nHe > 0.0 ? y2n : y2;
+        y3n = nHe > 0.0 ? y3n : y3;
     }
     // ---- electron density check
     const double nen = xn * nH + (y2n + 2.0 * y3n) * nHe;
-    if (rel_above(nen, ne0, 0.1)) {
-        s.h = 0.5 * h;
-        return false;
-    }
-    small &= fabs(nen - ne0) < 0.05 * ne0;
-    // ---- accept
+    ok = ok && !rel_above(nen, ne0, 0.1);
+    small = small && fabs(nen - ne0) < 0.05 * ne0;
+    // ---- accept, or halve
+    if (ok) {
 #pragma unroll
-    for (int g = 0; g < M; ++g) {
-        s.N[g] = Nn[g];
-        s.fs[g] *= rd[g];
-        if constexpr (SM) s.fb[g] = (s.fb[g] + h) * rd[g];
+        for (int g = 0; g < M; ++g) {
+            s.N[g] = Nn[g];
+            s.fs[g] *= rd[g];
+            if constexpr (SM) s.fb[g] = (s.fb[g] + h) * rd[g];
+        }
+        s.x = xn;
+        s.y2 = y2n;
+        s.y3 = y3n;
+        s.Tmu = iso ? cc.Tiso * imu_of(k, xn, y2n, y3n) : Tmun;
+        s.rem -= h;
+        ++s.acc;
     }
-    s.x = xn;
-    s.y2 = y2n;
-    s.y3 = y3n;
-    s.Tmu = iso ? cc.Tiso / mu_of(k, xn, y2n, y3n) : Tmun;
-    s.rem -= h;
-    ++s.acc;
-    s.h = small ? 2.0 * h : h;
-    return !(s.rem > 0.0);
+    if (live) s.h = ok ? (small ? 2.0 * h : h) : 0.5 * h;
+    return capped || (ok && !(s.rem > 0.0));
 }
 
 template <int M, class S>
@@ -538,26 +600,30 @@ constexpr unsigned TAIL_CHUNK = RT_TAIL_CHUNK;
 #endif
 constexpr unsigned CHEM_SWEEP_CHUNK = RT_CHEM_SWEEP_CHUNK;
 
-__device__ __forceinline__ void q_store_rates(const QueueView &q, uint32_t p, const CS &) {}
-__device__ __forceinline__ void q_store_rates(const QueueView &q, uint32_t p, const CSR &s)
+template <class S>
+__device__ __forceinline__ void q_store_rates(const QueueView &q, uint32_t p, const S &s)
 {
-    double *v = q.v + p;
-    const size_t c = q.stride;
+    if constexpr (S::smooth) {
+        double *v = q.v + p;
+        const size_t c = q.stride;
 #pragma unroll
-    for (int g = 0; g < 3; ++g) {
-        v[(size_t)(QV_GRID + g) * c] = s.Nr[g];
-        v[(size_t)(QV_GRID + 3 + g) * c] = s.fb[g];
+        for (int g = 0; g < 3; ++g) {
+            v[(size_t)(QV_GRID + g) * c] = s.Nr[g];
+            v[(size_t)(QV_GRID + 3 + g) * c] = s.fb[g];
+        }
     }
 }
-__device__ __forceinline__ void q_load_rates(const QueueView &q, uint32_t p, CS &) {}
-__device__ __forceinline__ void q_load_rates(const QueueView &q, uint32_t p, CSR &s)
+template <class S>
+__device__ __forceinline__ void q_load_rates(const QueueView &q, uint32_t p, S &s)
 {
-    const double *v = q.v + p;
-    const size_t c = q.stride;
+    if constexpr (S::smooth) {
+        const double *v = q.v + p;
+        const size_t c = q.stride;
 #pragma unroll
-    for (int g = 0; g < 3; ++g) {
-        s.Nr[g] = v[(size_t)(QV_GRID + g) * c];
-        s.fb[g] = v[(size_t)(QV_GRID + 3 + g) * c];
+        for (int g = 0; g < 3; ++g) {
+            s.Nr[g] = v[(size_t)(QV_GRID + g) * c];
+            s.fb[g] = v[(size_t)(QV_GRID + 3 + g) * c];
+        }
     }
 }
 
@@ -610,18 +676,16 @@ __device__ __forceinline__ uint32_t q_load(const KChem &k, const QueueView &q, u
 
 // Flux of group g of a finished cell from the transported flux fp in the
 // destination (and, smoothed, the pre-step flux ft of the source set).
-template <typename R>
-__device__ __forceinline__ R finish_flux(const ChemIO<R> &io, const CS &s, int g, R fp, R ft)
+template <typename R, class S>
+__device__ __forceinline__ R finish_flux(const ChemIO<R> &io, const S &s, int g, R fp, R ftr)
 {
-    return (R)((double)fp * s.fs[g]);
-}
-template <typename R>
-__device__ __forceinline__ R finish_flux(const ChemIO<R> &io, const CSR &s, int g, R fp, R ftr)
-{
-    // a cell that accepted no substep keeps its pre-step state
-    const double ft = (double)ftr;
-    if (s.acc == 0) return (R)ft;
-    return (R)(s.fs[g] * ft + s.fb[g] * (((double)fp - ft) / io.sm.dt));
+    if constexpr (S::smooth) {
+        // a cell that accepted no substep keeps its pre-step state
+        const double ft = (double)ftr;
+        if (s.acc == 0) return (R)ft;
+        return (R)(s.fs[g] * ft + s.fb[g] * (((double)fp - ft) / io.sm.dt));
+    } else
+        return (R)((double)fp * s.fs[g]);
 }
 
 // The previous-pass attempt count kept per cell: the count, capped at 127,
@@ -639,7 +703,7 @@ template <typename R, int M, bool LOADED, class S>
 __device__ __forceinline__ void store_cell_impl(const ChemIO<R> &io, uint32_t i, const S &s, double T,
                                                 const R *fpin, uint8_t mark)
 {
-    constexpr bool SM = std::is_same<S, CSR>::value;
+    constexpr bool SM = S::smooth;
     const size_t nc = io.ncell;
     R fp[3 * M], ft[3 * M];
 #pragma unroll

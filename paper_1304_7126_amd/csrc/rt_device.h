@@ -2,16 +2,14 @@
 //
 // Closure (Sec. 2, eqs. edd2/eddTens/Udir), intercell fluxes (Sec. 3.2,
 // eqs. glf/hll) and the App. E rate coefficients with their T-derivatives.
-// Rates are evaluated from one ln T, sqrt(T) and 1/T per temperature:
-// powers become exp(p ln lambda), the Hui & Gnedin denominators
-// exp(-r ln(1 + (lambda/l0)^q)), and derivatives come from logarithmic
-// derivatives (dv/dT = v/T * dln v/dln T).  The logarithms are those of
-// rt_math.h.
+// The smooth rates come from the piecewise polynomials of rt_rates.h, the
+// Boltzmann factors from one sqrt(T) and 1/T per temperature.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
 #include "rt_math.h"
+#include "rt_rates.h"
 
 // Multiplies and adds are fused into FMAs only where they form one source
 // expression (a * b + c): the front end marks exactly those, and the
@@ -225,24 +223,20 @@ __device__ __forceinline__ void hll_speeds(const R *__restrict__ tab, int nf, in
 
 // ---------------------------------------------------------------------
 // App. E rate coefficients, case B (on-the-spot approximation, Sec. 3.3.2)
-// and case A (without it).  vd holds value v and derivative d = dv/dT.
+// or case A (without it).  vd holds value v and derivative d = dv/dT.  The
+// Hui & Gnedin fits and powers of T come from the piecewise polynomials of
+// rt_rates.h; the Boltzmann factors of collisional ionisation and excitation
+// are computed here.
 // ---------------------------------------------------------------------
 struct vd {
     double v, d;
 };
 
-// per-temperature shared quantities
-struct Tq {
-    double T, lnT, invT, sqT, s5, g;  // sqT = sqrt(T), s5 = sqrt(T/1e5), g = 1/(1+s5)
-};
-
 // sqrt(T) and 1/T from the hardware reciprocal square root r: g = T r and
 // h = r/2 approach sqrt(T) and 1/(2 sqrt(T)); one Goldschmidt step on both,
 // then a Newton correction of g from its residual T - g^2 and one more step
-// on h, leave each within an ulp, and 1/T = (2h)^2.  A temperature that is
-// not positive and finite (only an input can be: the 10 % rule keeps the
-// substeps' temperatures within 10 % of each other) takes the IEEE square
-// root and division, in a branch no wave enters otherwise.
+// on h, leave each within an ulp, and 1/T = (2h)^2.  (Zero or negative T
+// gives NaN, and an attempt that fails.)
 __device__ __forceinline__ void sqrt_and_inv(double T, double &sq, double &inv)
 {
     const double r = __builtin_amdgcn_rsq(T);
@@ -257,180 +251,214 @@ __device__ __forceinline__ void sqrt_and_inv(double T, double &sq, double &inv)
     const double h2 = h + h;
     sq = g;
     inv = h2 * h2;
-    if (!(T > 0.0 && T < INFINITY)) {
-        sq = sqrt(T);
-        inv = 1.0 / T;
-    }
 }
 
+// The smooth rates of the case in use (CA: case A) at one temperature after
+// another, from the table x in global memory or (LDS) its copy l in LDS.
+//
+// The pointer to the global table comes out of a structure in memory; it is
+// given its address space here, so that its reads are global (or, of the
+// exponential's coefficients, which every lane shares, scalar) and not flat.
+typedef const __attribute__((address_space(1))) double *gptr;
+typedef const __attribute__((address_space(4))) double *sptr;
+
+template <bool CA, bool LDS>
+struct Rates {
+    gptr x;
+    const double *l;
+    __device__ __forceinline__ Rates(const double *xx, const double *ll) : x((gptr)xx), l(ll) {}
+
+    // The exponential's coefficients: scalar loads in the block that uses them
+    // (the empty asm keeps them from being hoisted out of the subcycling loop,
+    // where they would cost registers the loop does not have)
+    __device__ __forceinline__ sptr expc() const
+    {
+        const uint64_t a = (uint64_t)x + RTX::X * sizeof(double);
+        uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)a);
+        const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(a >> 32));
+        asm volatile("" : "+s"(lo));
+        return (sptr)((uint64_t)hi << 32 | lo);
+    }
+
+    // the coefficients of the fit at offset OX of the global table, OL of the
+    // copy; a lane outside the copy reads the global one (a branch no wave of
+    // an ordinary run enters)
+    template <int OX, int OL>
+    __device__ __forceinline__ RateCoef fit(const RateAt &a) const
+    {
+        if constexpr (!LDS) return rate_coef<RT_XNI>(x + OX, a.n);
+        const uint32_t n = a.n - (uint32_t)RT_LOFF;
+        RateCoef c = rate_coef<RT_LNI>(l + OL, n < (uint32_t)RT_LNI ? n : 0u);
+        if (__builtin_expect(n >= (uint32_t)RT_LNI, 0)) c = rate_coef<RT_XNI>(x + OX, a.n);
+        return c;
+    }
+    template <int OX, int OL>
+    __device__ __forceinline__ RateCoef mantissa(const RateAt &a) const
+    {
+        if constexpr (LDS) return rate_coef<RT_SUB>(l + OL, a.n % RT_SUB);
+        else return rate_coef<RT_SUB>(x + OX, a.n % RT_SUB);
+    }
+    template <int OX, int OL>
+    __device__ __forceinline__ double octave(const RateAt &a) const
+    {
+        const uint32_t o = a.n / RT_SUB;
+        if constexpr (!LDS) return x[OX + o];
+        const uint32_t n = o - (uint32_t)(RT_LOFF / RT_SUB);
+        double v = l[OL + (n < (uint32_t)RT_LNOCT ? n : 0u)];
+        if (__builtin_expect(n >= (uint32_t)RT_LNOCT, 0)) v = x[OX + o];
+        return v;
+    }
+
+    // recombination cooling of HII, HeII (without d/dT: a power of T) and HeIII
+    __device__ __forceinline__ void cooling(double T, vd &eHII, double &eHeII, vd &eHeIII, RateAt &at) const
+    {
+        at = rate_at(T);
+        const RateAt a3 = rate_at(RT_HEIII_SCALE * T);
+        RateCoef c = fit<RTX::E, RTL::E>(at), c3 = fit<RTX::E, RTL::E>(a3), cp = mantissa<RTX::P, RTL::P>(at);
+        const double po = octave<RTX::PO, RTL::PO>(at);
+        loaded(c, c3);
+        eHII.v = rate_poly_d(c, at.z, eHII.d);
+        eHII.d *= at.sc;
+        eHeIII.v = (8.0 / RT_HEIII_SCALE) * rate_poly_d(c3, a3.z, eHeIII.d);
+        eHeIII.d *= 8.0 * a3.sc;
+        loaded(cp);
+        eHeII = KB * T * (po * rate_poly(cp, at.z));
+    }
+    // T^-0.397 (at: as cooling() returned it for T)
+    __device__ __forceinline__ double t397(const RateAt &at) const
+    {
+        RateCoef c = mantissa<RTX::Q, RTL::Q>(at);
+        const double qo = octave<RTX::QO, RTL::QO>(at);
+        loaded(c);
+        return qo * rate_poly(c, at.z);
+    }
+    __device__ __forceinline__ vd alpha_HII(double T) const
+    {
+        const RateAt at = rate_at(T);
+        RateCoef c = fit<RTX::A, RTL::A>(at);
+        loaded(c);
+        vd a;
+        a.v = rate_poly_d(c, at.z, a.d);
+        a.d *= at.sc;
+        return a;
+    }
+    __device__ __forceinline__ void alpha_He(double T, double &aHeII, double &aHeIII) const
+    {
+        const RateAt at = rate_at(T), a3 = rate_at(RT_HEIII_SCALE * T);
+        RateCoef c3 = fit<RTX::A, RTL::A>(a3), cp = mantissa<RTX::P, RTL::P>(at);
+        const double po = octave<RTX::PO, RTL::PO>(at);
+        loaded(c3, cp);
+        aHeII = po * rate_poly(cp, at.z);
+        aHeIII = 2.0 * rate_poly(c3, a3.z);
+    }
+    __device__ __forceinline__ double alpha_HeIII(double T) const
+    {
+        const RateAt a3 = rate_at(RT_HEIII_SCALE * T);
+        RateCoef c = fit<RTX::A, RTL::A>(a3);
+        loaded(c);
+        return 2.0 * rate_poly(c, a3.z);
+    }
+    // alpha_A - alpha_B of HII, HeII and HeIII (the table of a case A context)
+    __device__ __forceinline__ void excess(double T, double e[3]) const
+    {
+        const RateAt at = rate_at(T), a3 = rate_at(RT_HEIII_SCALE * T);
+        RateCoef c = fit<RTX::DA, RTL::DA>(at);
+        loaded(c);
+        e[0] = rate_poly(c, at.z);
+        c = fit<RTX::DA, RTL::DA>(a3);
+        loaded(c);
+        e[2] = 2.0 * rate_poly(c, a3.z);
+        c = mantissa<RTX::P, RTL::P>(at);
+        loaded(c);
+        e[1] = octave<RTX::PO, RTL::PO>(at) * rate_poly(c, at.z);
+        c = mantissa<RTX::PB, RTL::PB>(at);
+        loaded(c);
+        e[1] -= octave<RTX::PBO, RTL::PBO>(at) * rate_poly(c, at.z);
+    }
+};
+
+// Below these temperatures exp(-Tj/T) underflows to exactly zero (its
+// argument is below -745.14): 94,000 K / T for every Boltzmann factor of the
+// cooling, the ionisation temperatures of HI, HeI and HeII for the rates.  A
+// wave whose lanes are all below skips them; in a wave that does not, such a
+// lane computes the same zero.  Nine attempts in ten of the lognormal boxes
+// are in gas below 126 K: a front cell stays cold until its ionised fraction
+// passes about a hundredth, which takes most of its substeps.
+constexpr double T_COLD_COOL = 126.0, T_COLD_HI = 211.0, T_COLD_HEI = 382.0, T_COLD_HEII = 847.0;
+
+// sqrt(T), 1/T, s5 = sqrt(T/1e5) and g = 1/(1+s5)
+struct Tq {
+    double sqT, invT, s5, g;
+};
 __device__ __forceinline__ Tq make_Tq(double T)
 {
     Tq q;
-    q.T = T;
-    q.lnT = rt_log(T);
     sqrt_and_inv(T, q.sqT, q.invT);
     q.s5 = q.sqT * 3.1622776601683795e-3;  // sqrt(1e-5)
     q.g = rcp_pos(1.0 + q.s5);
     return q;
 }
 
-// A sqrt(T) (1+sqrt(T/1e5))^-1 exp(-Tj/T)      (E.1 and the zeta of E.3)
-__device__ __forceinline__ vd r_cen(const Tq &q, double A, double Tj)
+// A sqrt(T) (1+sqrt(T/1e5))^-1 exp(-Tj/T)      (E.1)
+__device__ __forceinline__ vd r_cen(sptr ec, const Tq &q, double A, double Tj)
 {
     vd o;
-    o.v = A * q.sqT * q.g * exp(-Tj * q.invT);
+    o.v = A * q.sqT * q.g * exp_neg(ec, -Tj * q.invT);
     const double dl = 0.5 - 0.5 * q.s5 * q.g + Tj * q.invT;  // dln v / dln T
     o.d = o.v * dl * q.invT;
     return o;
 }
 
-// A lam^p / (1+(lam/l0)^q)^r, lam = TL/T     (E.2 Hui & Gnedin)
-__device__ __forceinline__ vd r_hg(const Tq &q, double A, double lnTL, double p, double lnl0, double qq,
-                                   double r)
-{
-    const double lnlam = lnTL - q.lnT;
-    const double u = exp(qq * (lnlam - lnl0));
-    vd o;
-    o.v = A * exp(p * lnlam - r * rt_log1p(u));
-    const double dlnlam = p - r * qq * div_pos(u, 1.0 + u);  // dln v / dln lam
-    o.d = -o.v * dlnlam * q.invT;
-    return o;
-}
-
-// B T lam^p / (1+(lam/l0)^q)^r    (E.3 recombination cooling)
-__device__ __forceinline__ vd r_hgc(const Tq &q, double B, double lnTL, double p, double lnl0, double qq,
-                                    double r)
-{
-    const double lnlam = lnTL - q.lnT;
-    const double u = exp(qq * (lnlam - lnl0));
-    vd o;
-    o.v = B * q.T * exp(p * lnlam - r * rt_log1p(u));
-    const double dlnlam = p - r * qq * div_pos(u, 1.0 + u);
-    o.d = o.v * (1.0 - dlnlam) * q.invT;
-    return o;
-}
-
-// A lam^p
-__device__ __forceinline__ vd r_pw(const Tq &q, double A, double lnTL, double p)
-{
-    vd o;
-    o.v = A * exp(p * (lnTL - q.lnT));
-    o.d = -p * o.v * q.invT;
-    return o;
-}
-
-// ln of the Hui & Gnedin threshold temperatures and break points
-constexpr double LN_TL_HI = 12.662275226919286;    // ln 315614
-constexpr double LN_TL_HEI = 13.254566388120152;   // ln 570670
-constexpr double LN_TL_HEII = 14.049024154019651;  // ln 1263030
-constexpr double LN_2p74 = 1.007957920399979;
-constexpr double LN_2p25 = 0.8109302162163288;
-
-__device__ __forceinline__ vd beta_HI(const Tq &q) { return r_cen(q, 5.85e-11, 157809.1); }
-__device__ __forceinline__ vd beta_HeI(const Tq &q) { return r_cen(q, 2.38e-11, 285335.4); }
-__device__ __forceinline__ vd beta_HeII(const Tq &q) { return r_cen(q, 5.68e-12, 631515.0); }
-
-__device__ __forceinline__ vd alphaB_HII(const Tq &q)
-{
-    return r_hg(q, 2.753e-14, LN_TL_HI, 1.5, LN_2p74, 0.407, 2.242);
-}
-__device__ __forceinline__ vd alphaB_HeII(const Tq &q) { return r_pw(q, 1.26e-14, LN_TL_HEI, 0.75); }
-__device__ __forceinline__ vd alphaB_HeIII(const Tq &q)
-{
-    return r_hg(q, 5.506e-14, LN_TL_HEII, 1.5, LN_2p74, 0.407, 2.242);
-}
-
-// case A (E.2): recombinations to every level
-constexpr double LN_0p522 = -0.6500876910994983;
-constexpr double LN_0p541 = -0.6143360001356555;
-__device__ __forceinline__ vd alphaA_HII(const Tq &q)
-{
-    return r_hg(q, 1.269e-13, LN_TL_HI, 1.503, LN_0p522, 0.47, 1.923);
-}
-__device__ __forceinline__ vd alphaA_HeII(const Tq &q) { return r_pw(q, 3e-14, LN_TL_HEI, 0.654); }
-__device__ __forceinline__ vd alphaA_HeIII(const Tq &q)
-{
-    return r_hg(q, 2.538e-13, LN_TL_HEII, 1.503, LN_0p522, 0.47, 1.923);
-}
-
-// the recombination rates of the case in use: CA = case A (no OTSA)
-template <bool CA>
-__device__ __forceinline__ vd alpha_HII(const Tq &q) { return CA ? alphaA_HII(q) : alphaB_HII(q); }
-template <bool CA>
-__device__ __forceinline__ vd alpha_HeII(const Tq &q) { return CA ? alphaA_HeII(q) : alphaB_HeII(q); }
-template <bool CA>
-__device__ __forceinline__ vd alpha_HeIII(const Tq &q) { return CA ? alphaA_HeIII(q) : alphaB_HeIII(q); }
-
-// (lambda_HeII / lambda_HI)^q = (1263030 / 315614)^q: the ratio of the Hui &
-// Gnedin terms (lambda/l0)^q of the HeIII and HII recombination-cooling fits
-// at one temperature, for the case B (q = 0.376) and case A (q = 0.502) fits
-constexpr double HG_COOL_U_RATIO = 1.6844137772424854;
-constexpr double HG_COOL_U_RATIO_A = 2.006010575388344;
+__device__ __forceinline__ vd beta_HI(sptr ec, const Tq &q) { return r_cen(ec, q, 5.85e-11, 157809.1); }
+__device__ __forceinline__ vd beta_HeI(sptr ec, const Tq &q) { return r_cen(ec, q, 2.38e-11, 285335.4); }
+__device__ __forceinline__ vd beta_HeII(sptr ec, const Tq &q) { return r_cen(ec, q, 5.68e-12, 631515.0); }
 
 // Primordial cooling L of eq. (rate_cooling) and dL/dT, with the case B
-// recombination cooling of the OTSA or (CA) the case A one.  Products of
-// exponentials are taken as one exponential of the summed arguments, and the
-// HeIII recombination term reuses the HII term's (lambda/l0)^q.
-template <bool CA>
-__device__ __forceinline__ void cooling(const Tq &q, double a_exp, double ne, double nHI, double nHII,
-                                        double nHeI, double nHeII, double nHeIII, double &L, double &dL)
+// recombination cooling of the OTSA or (CA) the case A one; Tcmb and cpk are
+// the temperature and the coefficient of the Compton term.
+template <bool CA, bool LDS>
+__device__ __forceinline__ void cooling(const Rates<CA, LDS> &r, double T, double Tcmb, double cpk, double ne, double nHI,
+                                        double nHII, double nHeI, double nHeII, double nHeIII, double &L, double &dL)
 {
-    const double sqT = q.sqT;
-    // collisional ionisation cooling (Cen form), three species
-    const double e1 = exp(-157809.1 * q.invT);
-    const double e2 = exp(-285335.4 * q.invT);
-    const double e3 = exp(-631515.0 * q.invT);
-    const double cbase = sqT * q.g;                              // sqrt(T)/(1+s5)
-    const double cdl = 0.5 - 0.5 * q.s5 * q.g;                   // dln(cbase)/dlnT
-    const double zHI = 1.27e-21 * cbase * e1, zHIl = cdl + 157809.1 * q.invT;
-    const double zHeI = 9.38e-22 * cbase * e2, zHeIl = cdl + 285335.4 * q.invT;
-    const double zHeII = 4.95e-22 * cbase * e3, zHeIIl = cdl + 631515.0 * q.invT;
-    // collisional excitation
-    const double gdl = -0.5 * q.s5 * q.g;
-    const double psHI = 7.5e-19 * q.g * exp(-118348.0 * q.invT), psHIl = gdl + 118348.0 * q.invT;
-    const double psHeII = 5.54e-17 * q.g * exp(-0.397 * q.lnT - 473638.0 * q.invT);
-    const double psHeIIl = -0.397 + gdl + 473638.0 * q.invT;
-    // recombination cooling: B T lam^p / (1 + (lam/l0)^q)^r for HII
-    // (lam = 315614/T) and HeIII (lam = 1263030/T, 8 B)
     vd eHII, eHeIII;
-    {
-        constexpr double B = CA ? 1.778e-29 : 3.435e-30;
-        constexpr double p = CA ? 1.965 : 1.97, qq = CA ? 0.502 : 0.376, r = CA ? 2.697 : 3.72;
-        constexpr double lnl0 = CA ? LN_0p541 : LN_2p25;
-        constexpr double ratio = CA ? HG_COOL_U_RATIO_A : HG_COOL_U_RATIO;
-        const double l1 = LN_TL_HI - q.lnT, l3 = LN_TL_HEII - q.lnT;
-        const double u1 = exp(qq * (l1 - lnl0));
-        const double u3 = u1 * ratio;
-        eHII.v = B * q.T * exp(p * l1 - r * rt_log1p(u1));
-        eHeIII.v = 8.0 * B * q.T * exp(p * l3 - r * rt_log1p(u3));
-        eHII.d = eHII.v * (1.0 - (p - r * qq * div_pos(u1, 1.0 + u1))) * q.invT;
-        eHeIII.d = eHeIII.v * (1.0 - (p - r * qq * div_pos(u3, 1.0 + u3))) * q.invT;
-    }
-    // eta_HeII = k_B T alpha_HeII
-    constexpr double pHe2 = CA ? 0.654 : 0.75;
-    const vd aHe2 = r_pw(q, CA ? 3e-14 : 1.26e-14, LN_TL_HEI, pHe2);
-    const double eHeII = KB * q.T * aHe2.v, eHeIIl = 1.0 - pHe2;
-    // dielectronic recombination
-    const double ed2 = exp(-94000.0 * q.invT);
-    const double om = 1.24e-13 * exp(-1.5 * q.lnT - 470000.0 * q.invT) * (1.0 + 0.3 * ed2);
-    const double oml = -1.5 + 470000.0 * q.invT + div_pos(0.3 * ed2 * 94000.0 * q.invT, 1.0 + 0.3 * ed2);
-    // bremsstrahlung and Compton
-    const double th = 1.42e-27 * sqT;
-    const double Tg = 2.727 / a_exp;
-    const double Tg2 = Tg * Tg;
-    const double cpk = 1.017e-37 * Tg2 * Tg2;
-    const double cp = cpk * (q.T - Tg);
-
+    double eHeII, sqT, invT;
+    RateAt at;
+    r.cooling(T, eHII, eHeII, eHeIII, at);
+    sqrt_and_inv(T, sqT, invT);
     const double cHI = ne * nHI, cHeI = ne * nHeI, cHeII = ne * nHeII;
     const double cHII = ne * nHII, cHeIII = ne * nHeIII;
+    constexpr double eHeIIl = 1.0 - (CA ? 0.654 : 0.75);
+    // bremsstrahlung and Compton
+    const double th = 1.42e-27 * sqT;
+    const double cp = cpk * (T - Tcmb);
     const double brn = ne * (nHII + nHeII + 4.0 * nHeIII);
-    L = (zHI + psHI) * cHI + zHeI * cHeI + (zHeII + psHeII + eHeII + om) * cHeII + eHII.v * cHII +
-        eHeIII.v * cHeIII + th * brn + cp * ne;
-    // d/dT: value * dln/dlnT / T for the log-derivative terms
-    const double dlog = (zHI * zHIl + psHI * psHIl) * cHI + zHeI * zHeIl * cHeI +
-                        (zHeII * zHeIIl + psHeII * psHeIIl + eHeII * eHeIIl + om * oml) * cHeII +
-                        0.5 * th * brn;
-    dL = dlog * q.invT + eHII.d * cHII + eHeIII.d * cHeIII + cpk * ne;
+    L = eHeII * cHeII + eHII.v * cHII + eHeIII.v * cHeIII + th * brn + cp * ne;
+    // value * dln/dlnT of the terms without a d/dT of their own
+    double dlog = eHeII * eHeIIl * cHeII + 0.5 * th * brn;
+    if (!(T <= T_COLD_COOL)) {
+        const sptr ec = r.expc();
+        // collisional ionisation cooling (Cen form), three species
+        const double s5 = sqT * 3.1622776601683795e-3;
+        const double g = rcp_pos(1.0 + s5);
+        const double cbase = sqT * g;          // sqrt(T)/(1+s5)
+        const double gdl = -0.5 * s5 * g;      // dln g / dln T
+        const double cdl = 0.5 + gdl;          // dln(cbase)/dlnT
+        const double zHI = 1.27e-21 * cbase * exp_neg(ec, -157809.1 * invT), zHIl = cdl + 157809.1 * invT;
+        const double zHeI = 9.38e-22 * cbase * exp_neg(ec, -285335.4 * invT), zHeIl = cdl + 285335.4 * invT;
+        const double zHeII = 4.95e-22 * cbase * exp_neg(ec, -631515.0 * invT), zHeIIl = cdl + 631515.0 * invT;
+        // collisional excitation
+        const double psHI = 7.5e-19 * g * exp_neg(ec, -118348.0 * invT), psHIl = gdl + 118348.0 * invT;
+        const double psHeII = 5.54e-17 * g * r.t397(at) * exp_neg(ec, -473638.0 * invT);
+        const double psHeIIl = -0.397 + gdl + 473638.0 * invT;
+        // dielectronic recombination
+        const double ed2 = 0.3 * exp_neg(ec, -94000.0 * invT);
+        const double om = 1.24e-13 * (invT * invT * sqT) * exp_neg(ec, -470000.0 * invT) * (1.0 + ed2);
+        const double oml = -1.5 + 470000.0 * invT + div_pos(ed2 * 94000.0 * invT, 1.0 + ed2);
+        L += (zHI + psHI) * cHI + zHeI * cHeI + (zHeII + psHeII + om) * cHeII;
+        dlog += (zHI * zHIl + psHI * psHIl) * cHI + zHeI * zHeIl * cHeI +
+                (zHeII * zHeIIl + psHeII * psHeIIl + om * oml) * cHeII;
+    }
+    dL = dlog * invT + eHII.d * cHII + eHeIII.d * cHeIII + cpk * ne;
 }
 
 }  // namespace rtm1

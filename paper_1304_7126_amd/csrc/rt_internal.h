@@ -31,8 +31,12 @@ struct KChem {
     double x_min;
     double N_floor;
     long long max_att;
+    int max_att32;  // max_att, at most INT_MAX (the counters' range)
+    double HeH;     // helium per hydrogen nucleus, Y / (4 X)
     int otsa;           // 1: on-the-spot approximation; 0: case A with recombination photons
     double brec[3][3];  // [group][HII, HeII, HeIII]: 1 where the species' recombination photons go
+    double Tcmb, compton; // temperature and coefficient of the Compton term at a_exp (kchem_derive)
+    const double *rates;  // device table of the rate coefficients of the case in use (rt_rates.h)
 };
 
 // device statistics block (in library memory)
@@ -155,11 +159,6 @@ struct ChemIO {
 };
 
 constexpr int TAIL_BLOCKS = 1024;
-// workgroups of the one-pass chemistry kernel (persistent; 256 threads each)
-#ifndef RT_CHEM_ALL_BLOCKS
-#define RT_CHEM_ALL_BLOCKS 1024
-#endif
-constexpr int CHEM_ALL_BLOCKS = RT_CHEM_ALL_BLOCKS;
 constexpr int HEAD_ATTEMPTS = 3;
 
 // bytes of scratch for a queue of cap cells (after the reduction partials),
@@ -197,15 +196,25 @@ hipError_t launch_reduce(bool fp32, size_t ncell, int M, double c, double V, con
 // ionisation energies of HI, HeI, HeII [erg] (App. E.4)
 constexpr double EPS_ION_ERG[3] = {13.60 * 1.602176634e-12, 24.59 * 1.602176634e-12, 54.42 * 1.602176634e-12};
 
-// fill the derived per-photon rates csN, hc from cr, sN, sE, eb
+// fill the derived per-photon rates csN, hc from cr, sN, sE, eb, and the
+// Compton term from a_exp
 inline void kchem_derive(KChem &k)
 {
+    k.max_att32 = k.max_att < 2147483647LL ? (int)k.max_att : 2147483647;
+    k.HeH = k.Y / (4.0 * k.X);
+    k.Tcmb = 2.727 / k.a_exp;
+    const double T2 = k.Tcmb * k.Tcmb;
+    k.compton = 1.017e-37 * T2 * T2;
     for (int g = 0; g < 3; ++g)
         for (int j = 0; j < 3; ++j) {
             k.csN[g][j] = k.sN[g][j] * k.cr;
             k.hc[g][j] = k.cr * (k.eb[g] * k.sE[g][j] - EPS_ION_ERG[j] * k.sN[g][j]);
         }
 }
+
+// device copy of the rate table of the case in use (freed with hipFree); the
+// host tables are built on first use and kept (0.7 MB)
+hipError_t upload_rate_table(bool otsa, double **out);
 
 // differentiation form (rt_adjoint.hip)
 size_t adj_scan_parts(size_t nc);

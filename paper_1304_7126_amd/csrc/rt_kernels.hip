@@ -2,17 +2,13 @@
 //
 //   k_inject     point-source injection (Sec. 3.1)
 //   k_transport  unsplit GLF/HLL update of (N, F), all groups (Sec. 3.2)
-//   k_head       per-cell thermochemistry in FP64 (App. A), up to K attempts
-//                per cell; with FUSE the cell is transported first, so one
-//                pass reads the source set and writes the destination set
-//   k_tail       the cells still subcycling after the head pass, compacted
-//                into a queue and worked off by lanes that refill themselves
+//   the dispatch of the thermochemistry kernels (rt_chem.hip)
 //   k_reduce_*   photon budget and diagnostics (fixed-order tree sums)
 //
 // Radiation arrays are structure-of-arrays, x fastest, one plane of ncell
 // values per group and component, so a wavefront reads 64 consecutive cells
 // of one component with one coalesced access.
-#include "rt_cell.h"
+#include "rt_chem.h"
 
 namespace rtm1 {
 
@@ -83,26 +79,6 @@ hipError_t launch_source_map(int32_t *map, size_t ncell, const int32_t *cell, in
 unsigned acct_blocks(size_t ncell) { return (unsigned)((ncell + ACCT_THREADS - 1) / ACCT_THREADS); }
 size_t acct_bytes(size_t ncell) { return ((size_t)acct_blocks(ncell) * 6 * sizeof(double) + 255) & ~(size_t)255; }
 
-// Fixed-order block sum of the per-thread values v[0..5] (transported N and
-// outward boundary flux per group) into part[6 * blockIdx.x + q].  Called by
-// every thread of a 256-thread block.
-__device__ __forceinline__ void block_acct(double *part, const double v[6])
-{
-    __shared__ double sh[6][ACCT_THREADS];
-    const int t = threadIdx.x;
-#pragma unroll
-    for (int q = 0; q < 6; ++q) sh[q][t] = v[q];
-    __syncthreads();
-    for (int o = ACCT_THREADS / 2; o > 0; o >>= 1) {
-        if (t < o) {
-#pragma unroll
-            for (int q = 0; q < 6; ++q) sh[q][t] += sh[q][t + o];
-        }
-        __syncthreads();
-    }
-    if (t < 6) part[(size_t)6 * blockIdx.x + t] = sh[t][0];
-}
-
 // --------------------------------------------------------------- transport
 template <typename R, int FLUX>
 __global__ __launch_bounds__(256) void k_transport(KGrid g, int M, R c, R kdx, const R *__restrict__ Nin,
@@ -154,540 +130,14 @@ hipError_t launch_transport(bool fp32, int flux, const KGrid &g, int M, double c
 }
 
 // --------------------------------------------------------- thermochemistry
-// Per-block reduction of the chemistry counters; one atomic per block.
-__device__ __forceinline__ void block_stats(DevStats *st, unsigned long long acc, unsigned long long att,
-                                            unsigned long long mx, unsigned fl)
+template <typename R>
+static void launch_chem_pass(ChemPass pass, const KChem &kc, const ChemCall<R> &a, hipStream_t s)
 {
-    __shared__ unsigned long long s_acc[256], s_att[256], s_max[256];
-    __shared__ unsigned s_fl[256];
-    const int t = threadIdx.x + threadIdx.y * blockDim.x;
-    const int nt = blockDim.x * blockDim.y;
-    s_acc[t] = acc;
-    s_att[t] = att;
-    s_max[t] = mx;
-    s_fl[t] = fl;
-    __syncthreads();
-    for (int o = nt / 2; o > 0; o >>= 1) {
-        if (t < o) {
-            s_acc[t] += s_acc[t + o];
-            s_att[t] += s_att[t + o];
-            s_max[t] = s_max[t] > s_max[t + o] ? s_max[t] : s_max[t + o];
-            s_fl[t] |= s_fl[t + o];
-        }
-        __syncthreads();
-    }
-    if (t == 0) {
-        if (s_att[0]) {
-            atomicAdd(&st->acc_total, s_acc[0]);
-            atomicAdd(&st->att_total, s_att[0]);
-            atomicMax(&st->att_max, s_max[0]);
-        }
-        if (s_fl[0]) atomicOr(&st->flags, s_fl[0]);
-    }
-}
-
-__device__ __forceinline__ int lane_id() { return (int)(threadIdx.x & 63u); }
-
-// Histogram of accepted substeps per cell (bin 63: 63 or more), counted in
-// LDS per block and added to the device statistics at the end of the block.
-__device__ __forceinline__ void hist_init(unsigned *sh)
-{
-    if (threadIdx.x < 64) sh[threadIdx.x] = 0u;
-    __syncthreads();
-}
-__device__ __forceinline__ void hist_add(unsigned *sh, int acc) { atomicAdd(&sh[acc < 63 ? acc : 63], 1u); }
-__device__ __forceinline__ void hist_flush(const unsigned *sh, unsigned long long *hist)
-{
-    __syncthreads();
-    if (threadIdx.x < 64 && sh[threadIdx.x]) atomicAdd(&hist[threadIdx.x], (unsigned long long)sh[threadIdx.x]);
-}
-
-// Head pass: one thread per cell.  With FUSE the cell is first transported
-// (all groups, source set -> registers); then up to K chemistry attempts.
-// Cells that finish are written to the destination arrays; the rest go to
-// the queue (or, when it is full, finish in place).
-// Waves per SIMD the head kernel is compiled for: three (168 VGPRs, a few
-// bytes of spill) measured faster than two without spills, also for the
-// FP64 three-group variant (191 VGPRs at two waves: 8.7 -> 7.9 ms per head
-// launch at 256^3 x 3 once multiply-adds fuse per expression) and for the
-// smoothed one (140 bytes of spill at three: 6.9 against 7.5 ms at two).
-template <typename R, int M>
-constexpr int head_waves() { return 3; }
-
-// V selects the method variant of the chemistry (V_SMOOTH: it starts from
-// the radiation before injection and transport, io.sm, and takes their
-// change as a rate; V_CASE_A: no on-the-spot approximation).
-template <typename R, int M, int FUSE, int FLUX, int V>
-__global__ __launch_bounds__(256, (head_waves<R, M>())) void k_head(KGrid g, const KChem *__restrict__ kp, double dt, R c, R kdx, const R *__restrict__ Nin,
-                                              const R *__restrict__ Fin, ChemIO<R> io, const R *__restrict__ tab,
-                                              int nf, int nth, QueueView q, int K, DevStats *__restrict__ st)
-{
-    const KChem &k = *kp;
-    const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-    const bool valid = i < (uint32_t)g.ncell;
-    const size_t nc = g.ncell;
-    constexpr bool SM = (V & V_SMOOTH) != 0;
-    std::conditional_t<SM, CSR, CS> s;
-    CC cc{1.0, 0.0, 0.0, 0.0};
-    bool done = true;
-    unsigned fl = 0;
-    double av[6] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
-    __shared__ unsigned s_hist[64];
-    if (io.hist) hist_init(s_hist);
-#pragma unroll
-    for (int grp = 0; grp < CM; ++grp) {
-        s.N[grp] = 0.0;
-        s.fs[grp] = 1.0;
-        if constexpr (SM) s.Nr[grp] = 0.0;
-    }
-    if (valid) {
-        bool fin = true;
-        if (FUSE) {
-            // transport of every group; the flux goes straight to the
-            // destination, where the chemistry rescales it at the end
-            int ix, iy, iz;
-            cell_coords(g, i, ix, iy, iz);
-            const Nbr nb = neighbours(g, i, ix, iy, iz);
-#pragma unroll
-            for (int grp = 0; grp < M; ++grp) {
-                double bout = 0.0;
-                const U4<R> o = transport_cell<R, FLUX>(nb, i, nc, Nin + (size_t)grp * nc,
-                                                        Fin + (size_t)3 * grp * nc, c, kdx, tab, nf, nth, bout, g,
-                                                        grp);
-                s.N[grp] = (double)o.n * io.ia3;
-                av[grp] = (double)o.n;
-                av[3 + grp] = bout;
-                io.F[(size_t)(3 * grp) * nc + i] = o.fx;
-                io.F[(size_t)(3 * grp + 1) * nc + i] = o.fy;
-                io.F[(size_t)(3 * grp + 2) * nc + i] = o.fz;
-                fin = fin && isfinite(o.fx) && isfinite(o.fy) && isfinite(o.fz);
-            }
-        } else {
-#pragma unroll
-            for (int grp = 0; grp < M; ++grp) {
-                s.N[grp] = (double)io.N[(size_t)grp * nc + i] * io.ia3;
-#pragma unroll
-                for (int d = 0; d < 3; ++d) fin = fin && isfinite(io.F[(size_t)(3 * grp + d) * nc + i]);
-            }
-        }
-        if constexpr (SM) {
-            // N^t from the pre-step set, or for a source cell its value
-            // before the injection; rate (N' - N^t)/dt (eq. smoothrate1)
-            const int si = io.sm.map ? io.sm.map[i] : -1;
-#pragma unroll
-            for (int grp = 0; grp < M; ++grp) {
-                const double nt = (si >= 0 ? io.sm.prev[(size_t)si * M + grp] : (double)io.sm.N[(size_t)grp * nc + i]) *
-                                  io.ia3;
-                s.Nr[grp] = (s.N[grp] - nt) / dt;
-                s.N[grp] = nt;
-#pragma unroll
-                for (int d = 0; d < 3; ++d) fin = fin && isfinite(io.sm.F[(size_t)(3 * grp + d) * nc + i]);
-            }
-        }
-        s.x = io.xHII[i];
-        s.y2 = io.xHeII[i];
-        s.y3 = io.xHeIII[i];
-        cc = make_cc(k, io.nH[i] * io.ia3, io.T[i]);
-        if (chem_init<CM, V>(k, dt, cc.Tiso, fin, s)) {
-            done = false;
-            for (int a = 0; a < K && !done; ++a) done = chem_attempt<CM, V, false>(k, cc, s, fl);
-        } else {
-            fl |= 2u;
-        }
-    }
-    if (FUSE && io.acct) block_acct(io.acct, av);
-    // wave-aggregated enqueue of the unfinished cells, by expected length of
-    // their chain of substeps: cells that took many attempts in the previous
-    // pass (the fronts move little in a step), then cells that accepted no
-    // substep in their K attempts here (a state that changes fast), then the
-    // rest.  The tail works the regions off in this order, so that the
-    // longest chains start first instead of draining the tail at its end.
-    const bool want = !done;
-    const int cls = !want ? 3
-                          : (io.prev_att && (io.prev_att[i] & ATT_MASK) >= TAIL_LONG_ATTEMPTS) ? 0
-                                                                                                 : (s.acc == 0 ? 1 : 2);
-    unsigned p = ~0u;
-#pragma unroll
-    for (int r = 0; r < 3; ++r) {
-        const bool cand = want && p == ~0u && cls <= r;  // a full region passes its cells on
-        const unsigned long long m = __ballot(cand);
-        if (m) {
-            const int leader = __ffsll((long long)m) - 1;
-            unsigned base = 0;
-            if (lane_id() == leader) base = atomicAdd(q.cnt[r], (unsigned)__popcll(m));
-            base = __shfl(base, leader);
-            if (cand) {
-                const unsigned k = base + (unsigned)__popcll(m & ((1ull << lane_id()) - 1ull));
-                if (k < q.rlen[r]) p = q.rbeg[r] + k;
-            }
-        }
-    }
-    bool queued = false;
-    if (p != ~0u) {
-        q_store(q, p, i, s, cc);
-        queued = true;
-    }
-    if (want && !queued) {
-        while (!done) done = chem_attempt<CM, V>(k, cc, s, fl);
-    }
-    unsigned long long a_acc = 0, a_att = 0;
-    if (valid && !queued) {
-        const double T = chem_finish<CM>(k, cc, s, fl);
-        store_cell<R, M>(io, i, s, T);
-        a_acc = (unsigned long long)s.acc;
-        a_att = (unsigned long long)s.att;
-        if (io.hist) hist_add(s_hist, s.acc);
-    }
-    if (io.hist) hist_flush(s_hist, io.hist);
-    block_stats(st, a_acc, a_att, a_att, fl);
-}
-
-// Tail pass over the queue: persistent waves whose lanes each take a queued
-// cell, run one attempt per loop trip (an attempt that fails the photon
-// check repeats at once with the halved substep), and refill from the
-// wave's reservation of queue positions as soon as their cell has filled
-// dt_RT, so that a few slow cells do not hold whole waves of finished
-// lanes.  Compiled for three waves per SIMD: the smoothed
-// variants would otherwise take 176-178 VGPRs and run two (a few bytes of
-// spill at three: 4.6 -> 4.0 ms per tail at 256^3 x 3).
-template <typename R, int M, int V>
-__global__ __launch_bounds__(256, 3) void k_tail(const KChem *__restrict__ kp, ChemIO<R> io, QueueView q, DevStats *__restrict__ st)
-{
-    const KChem &k = *kp;
-    // the regions in order: longest expected chains first
-    const unsigned n0 = min(*q.cnt[0], q.rlen[0]);
-    const unsigned n1 = min(*q.cnt[1], q.rlen[1]);
-    const unsigned n = n0 + n1 + min(*q.cnt[2], q.rlen[2]);
-    std::conditional_t<(V & V_SMOOTH) != 0, CSR, CS> s;
-    // the cell's destination fluxes, loaded with the cell (as in k_chem_all)
-    constexpr bool PRE = (V & V_SMOOTH) == 0;
-    R fpre[PRE ? 3 * M : 1];
-    uint32_t cell = 0;
-    CC cc{1.0, 0.0, 0.0, 0.0};
-    bool active = false, exhausted = false;
-    bool raised = false;
-    unsigned rbase = 0, ravail = 0;  // positions this wave has reserved and not yet handed out
-    unsigned fl = 0;
-    unsigned long long a_acc = 0, a_att = 0, a_max = 0;
-    __shared__ unsigned s_hist[64];
-    if (io.hist) hist_init(s_hist);
-    while (true) {
-        if (!exhausted) {
-            bool first = false;
-            const bool need = !active;
-            const unsigned long long m = __ballot(need);
-            if (m) {
-                const unsigned nneed = (unsigned)__popcll(m);
-                const unsigned r = (unsigned)__popcll(m & ((1ull << lane_id()) - 1ull));
-                unsigned t;
-                if (ravail >= nneed) {
-                    t = rbase + r;
-                    rbase += nneed;
-                    ravail -= nneed;
-                } else {
-                    // what is left of the reservation goes first; a new one
-                    // of at least TAIL_CHUNK positions covers the rest
-                    const unsigned more = nneed - ravail;
-                    const unsigned take = more > TAIL_CHUNK ? more : TAIL_CHUNK;
-                    const int leader = __ffsll((long long)m) - 1;
-                    unsigned base = 0;
-                    if (lane_id() == leader) base = atomicAdd(q.head, take);
-                    base = __shfl(base, leader);
-                    t = r < ravail ? rbase + r : base + (r - ravail);
-                    rbase = base + more;
-                    ravail = take - more;
-                }
-                // positions only grow: past n there is nothing left for this wave
-                if (rbase >= n) exhausted = true;
-                if (need && t < n) {
-                    const unsigned pos = t < n0 ? t : (t < n0 + n1 ? q.rbeg[1] + (t - n0) : q.rbeg[2] + (t - n0 - n1));
-                    cell = q_load(k, q, pos, s, cc);
-                    if constexpr (PRE) {
-#pragma unroll
-                        for (int j = 0; j < 3 * M; ++j) fpre[j] = io.F[(size_t)j * io.ncell + cell];
-                    }
-                    active = true;
-                    first = t < n0;
-                }
-            }
-            // a wave holding cells of the first region (the longest chains)
-            // issues ahead of the others for the rest of its life
-            if (!raised && __any(first)) {
-                __builtin_amdgcn_s_setprio(3);
-                raised = true;
-            }
-        }
-        if (!__any(active)) break;
-        if (active) {
-            if (chem_attempt<CM, V>(k, cc, s, fl)) {
-                const double T = chem_finish<CM>(k, cc, s, fl);
-                if constexpr (PRE) store_cell_with<R, M>(io, cell, s, T, fpre);
-                else store_cell<R, M>(io, cell, s, T);
-                if (io.hist) hist_add(s_hist, s.acc);
-                a_acc += (unsigned long long)s.acc;
-                a_att += (unsigned long long)s.att;
-                a_max = a_max > (unsigned long long)s.att ? a_max : (unsigned long long)s.att;
-                active = false;
-            }
-        }
-    }
-    if (io.hist) hist_flush(s_hist, io.hist);
-    block_stats(st, a_acc, a_att, a_max, fl);
-}
-
-__global__ void k_zero_u32(unsigned *p, int n)
-{
-    for (int k = threadIdx.x; k < n; k += blockDim.x) p[k] = 0u;
-}
-
-// Before the one-pass chemistry: the cells whose previous pass took at least
-// TAIL_LONG_ATTEMPTS attempts go to a list (the queue's cell array, as many
-// as it holds) that the pass takes first, and are marked ATT_LISTED; every
-// other mark is cleared.  The count of such cells goes to *cnt (it may
-// exceed cap).  A thread takes four consecutive cells (one 4-byte word of
-// counts; the array is padded to 256 bytes).
-__global__ __launch_bounds__(256) void k_long_list(uint8_t *__restrict__ prev, size_t nc, int32_t *__restrict__ list,
-                                                   unsigned cap, unsigned *__restrict__ cnt)
-{
-    const size_t q = (size_t)blockIdx.x * blockDim.x + threadIdx.x;  // word index
-    const size_t i0 = 4 * q;
-    uint32_t o = 0;
-    if (i0 < nc) o = reinterpret_cast<const uint32_t *>(prev)[q];
-    unsigned want = 0;  // bit j: cell i0 + j is a long chain
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const unsigned v = (o >> (8 * j)) & ATT_MASK;
-        if (i0 + j < nc && v >= (unsigned)TAIL_LONG_ATTEMPTS) want |= 1u << j;
-    }
-    // this lane's first slot: the wanted cells of the lanes before it
-    const unsigned c = (unsigned)__popc(want);
-    unsigned ex = c;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const unsigned u = __shfl_up(ex, d, 64);
-        if (lane_id() >= d) ex += u;
-    }
-    const unsigned tot = __shfl(ex, 63, 64);
-    ex -= c;
-    unsigned base = 0;
-    if (tot) {
-        if (lane_id() == 0) base = atomicAdd(cnt, tot);
-        base = __shfl(base, 0, 64);
-    }
-    uint32_t nw = 0;
-    unsigned k = base + ex;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        uint32_t b = (o >> (8 * j)) & ATT_MASK;
-        if (want & (1u << j)) {
-            if (k < cap) {
-                list[k] = (int32_t)(i0 + j);
-                b |= ATT_LISTED;
-            }
-            ++k;
-        }
-        nw |= b << (8 * j);
-    }
-    if (i0 < nc && nw != o) reinterpret_cast<uint32_t *>(prev)[q] = nw;
-}
-
-// The chemistry of every cell in one persistent launch (the pass after a
-// separate transport): each lane takes a cell, runs its attempts one per
-// loop trip (an attempt that fails the photon check repeats at once with the
-// halved substep), writes it when it has filled dt_RT and takes the next,
-// from its wave's reservation of positions.  Positions run over the list of
-// long chains first (their waves issue ahead of the others), then over all
-// cells in grid order, passing over the listed ones.  Every cell goes
-// through the same attempt code as in the head and tail passes, so results
-// are those of the two-pass chemistry bit for bit; what changes is that a
-// lane whose cell is done no longer idles until its wave's other lanes are.
-template <typename R, int M, int V>
-__global__ __launch_bounds__(256, 3) void k_chem_all(const KChem *__restrict__ kp, double dt, ChemIO<R> io, QueueView q,
-                                                     unsigned sweep_chunk, DevStats *__restrict__ st)
-{
-    const KChem &k = *kp;
-    constexpr bool SM = (V & V_SMOOTH) != 0;
-    const size_t nc = io.ncell;
-    const unsigned nl = io.prev_att ? min(*q.cnt[0], q.cap) : 0u;
-    const unsigned n = nl + (unsigned)nc;
-    std::conditional_t<SM, CSR, CS> s;
-    // the cell's destination fluxes, loaded with the cell (not with smoothed
-    // RT, whose larger state leaves no registers for them)
-    constexpr bool PRE = !SM;
-    R fpre[PRE ? 3 * M : 1];
-    uint32_t cell = 0;
-    CC cc{1.0, 0.0, 0.0, 0.0};
-    bool active = false, exhausted = false, raised = false;
-    uint8_t mark = 0;
-    unsigned rbase = 0, ravail = 0;  // positions this wave has reserved and not yet handed out
-    unsigned fl = 0, cfl = 0;        // flags of the lane, flags of its current cell
-    unsigned long long a_acc = 0, a_att = 0, a_max = 0;
-    __shared__ unsigned s_hist[64];
-    if (io.hist) hist_init(s_hist);
-    // the cell's state as the head pass loads it, without the check of its
-    // fluxes; returns chem_init's verdict
-    auto load = [&](uint32_t c, bool fin) -> bool {
-        const size_t i = c;
-#pragma unroll
-        for (int grp = 0; grp < CM; ++grp) {
-            s.N[grp] = 0.0;
-            s.fs[grp] = 1.0;
-            if constexpr (SM) s.Nr[grp] = 0.0;
-        }
-#pragma unroll
-        for (int grp = 0; grp < M; ++grp) s.N[grp] = (double)io.N[(size_t)grp * nc + i] * io.ia3;
-        if constexpr (SM) {
-            const int si = io.sm.map ? io.sm.map[i] : -1;
-#pragma unroll
-            for (int grp = 0; grp < M; ++grp) {
-                const double nt =
-                    (si >= 0 ? io.sm.prev[(size_t)si * M + grp] : (double)io.sm.N[(size_t)grp * nc + i]) * io.ia3;
-                s.Nr[grp] = (s.N[grp] - nt) / dt;
-                s.N[grp] = nt;
-#pragma unroll
-                for (int d = 0; d < 3; ++d) fin = fin && isfinite(io.sm.F[(size_t)(3 * grp + d) * nc + i]);
-            }
-        }
-        s.x = io.xHII[i];
-        s.y2 = io.xHeII[i];
-        s.y3 = io.xHeIII[i];
-        cc = make_cc(k, io.nH[i] * io.ia3, io.T[i]);
-        // the fluxes are needed only when the cell is written: loaded now,
-        // they arrive while the attempts run instead of stalling the wave
-        // at the write
-        if constexpr (PRE) {
-#pragma unroll
-            for (int j = 0; j < 3 * M; ++j) fpre[j] = io.F[(size_t)j * nc + i];
-        }
-        return chem_init<CM, V>(k, dt, cc.Tiso, fin, s);
-    };
-    // write a cell whose chemistry has ended.  Its fluxes are checked here,
-    // where they are used: a non-finite one means the cell is written back
-    // as loaded (what the head pass does when it finds one before the
-    // chemistry), and the flags of the discarded attempts are dropped
-    auto finish = [&]() {
-        bool fin = true;
-#pragma unroll
-        for (int j = 0; j < 3 * M; ++j) fin = fin && isfinite(PRE ? fpre[j] : io.F[(size_t)j * nc + cell]);
-        if (!fin) {
-            load(cell, false);
-            cfl = 2u;
-        }
-        fl |= cfl;
-        const double T = chem_finish<CM>(k, cc, s, fl);
-        if constexpr (PRE) store_cell_with<R, M>(io, cell, s, T, fpre, mark);
-        else store_cell<R, M>(io, cell, s, T, mark);
-        if (io.hist) hist_add(s_hist, s.acc);
-        a_acc += (unsigned long long)s.acc;
-        a_att += (unsigned long long)s.att;
-        a_max = a_max > (unsigned long long)s.att ? a_max : (unsigned long long)s.att;
-    };
-    while (true) {
-        if (!exhausted) {
-            bool first = false;
-            const bool need = !active;
-            const unsigned long long m = __ballot(need);
-            if (m) {
-                const unsigned nneed = (unsigned)__popcll(m);
-                const unsigned r = (unsigned)__popcll(m & ((1ull << lane_id()) - 1ull));
-                unsigned t;
-                if (ravail >= nneed) {
-                    t = rbase + r;
-                    rbase += nneed;
-                    ravail -= nneed;
-                } else {
-                    // one wave's width at a time among the long chains, so
-                    // that a wave does not hold a second set of them; more
-                    // in the sweep (sweep_chunk), where each reservation is
-                    // an atomic on the one counter every wave shares
-                    const unsigned more = nneed - ravail;
-                    const unsigned chunk = rbase < nl ? TAIL_CHUNK : sweep_chunk;
-                    const unsigned take = more > chunk ? more : chunk;
-                    const int leader = __ffsll((long long)m) - 1;
-                    unsigned base = 0;
-                    if (lane_id() == leader) base = atomicAdd(q.head, take);
-                    base = __shfl(base, leader);
-                    t = r < ravail ? rbase + r : base + (r - ravail);
-                    rbase = base + more;
-                    ravail = take - more;
-                }
-                if (rbase >= n) exhausted = true;
-                if (need && t < n) {
-                    bool take = true;
-                    if (t < nl) {
-                        cell = (uint32_t)q.cell[t];
-                        mark = ATT_LISTED;
-                        first = true;
-                    } else {
-                        cell = t - nl;
-                        mark = 0;
-                        take = !io.prev_att || !(io.prev_att[cell] & ATT_LISTED);
-                    }
-                    if (take) {
-                        cfl = 0;
-                        if (load(cell, true)) {
-                            active = true;
-                        } else {
-                            // a non-finite input: the cell is written back as loaded
-                            cfl = 2u;
-                            finish();
-                        }
-                    }
-                }
-            }
-            if (!raised && __any(first)) {
-                __builtin_amdgcn_s_setprio(3);
-                raised = true;
-            }
-        }
-        if (!__any(active)) {
-            if (exhausted) break;
-            continue;
-        }
-        if (active && chem_attempt<CM, V>(k, cc, s, cfl)) {
-            finish();
-            active = false;
-        }
-    }
-    if (io.hist) hist_flush(s_hist, io.hist);
-    block_stats(st, a_acc, a_att, a_max, fl);
-}
-
-// part 1: reset the queue counters and run the head pass; part 2: the tail
-template <typename R, int M, int FUSE, int FLUX, int V>
-static void launch_head_tail(int part, const KGrid &g, const KChem &kc, const KChem *dk, double dt, R c, R kdx, const void *Nin,
-                             const void *Fin, const ChemIO<R> &io, const void *tab, int nf, int nth,
-                             const QueueView &q, int K, DevStats *st, hipStream_t s)
-{
-    if (part == 1) {
-        hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(64), 0, s, q.count, 65);
-        hipLaunchKernelGGL((k_head<R, M, FUSE, FLUX, V>), dim3((unsigned)((g.ncell + 255) / 256)), dim3(256), 0, s, g,
-                           dk, dt, c, kdx, (const R *)Nin, (const R *)Fin, io, (const R *)tab, nf, nth, q, K, st);
-    } else {
-        hipLaunchKernelGGL((k_tail<R, M, V>), dim3(TAIL_BLOCKS), dim3(256), 0, s, dk, io, q, st);
-    }
-}
-
-template <typename R, int FUSE, int FLUX, int V>
-static void dispatch_M(int part, const KGrid &g, const KChem &kc, const KChem *dk, double dt, R c, R kdx, const void *Nin, const void *Fin,
-                       const ChemIO<R> &io, const void *tab, int nf, int nth, const QueueView &q, int K,
-                       DevStats *st, hipStream_t s)
-{
-    if (kc.M == 1) launch_head_tail<R, 1, FUSE, FLUX, V>(part, g, kc, dk, dt, c, kdx, Nin, Fin, io, tab, nf, nth, q, K, st, s);
-    else if (kc.M == 2) launch_head_tail<R, 2, FUSE, FLUX, V>(part, g, kc, dk, dt, c, kdx, Nin, Fin, io, tab, nf, nth, q, K, st, s);
-    else launch_head_tail<R, 3, FUSE, FLUX, V>(part, g, kc, dk, dt, c, kdx, Nin, Fin, io, tab, nf, nth, q, K, st, s);
-}
-
-template <typename R, int FUSE, int FLUX>
-static void dispatch_SM(int part, const KGrid &g, const KChem &kc, const KChem *dk, double dt, R c, R kdx, const void *Nin,
-                        const void *Fin, const ChemIO<R> &io, const void *tab, int nf, int nth, const QueueView &q,
-                        int K, DevStats *st, hipStream_t s)
-{
-    const int v = (io.sm.N ? V_SMOOTH : 0) | (kc.otsa ? 0 : V_CASE_A);
-    if (v == 0) dispatch_M<R, FUSE, FLUX, 0>(part, g, kc, dk, dt, c, kdx, Nin, Fin, io, tab, nf, nth, q, K, st, s);
-    else if (v == 1) dispatch_M<R, FUSE, FLUX, 1>(part, g, kc, dk, dt, c, kdx, Nin, Fin, io, tab, nf, nth, q, K, st, s);
-    else if (v == 2) dispatch_M<R, FUSE, FLUX, 2>(part, g, kc, dk, dt, c, kdx, Nin, Fin, io, tab, nf, nth, q, K, st, s);
-    else dispatch_M<R, FUSE, FLUX, 3>(part, g, kc, dk, dt, c, kdx, Nin, Fin, io, tab, nf, nth, q, K, st, s);
+    const int v = (a.io.sm.N ? V_SMOOTH : 0) | (kc.otsa ? 0 : V_CASE_A);
+    if (v == 0) launch_chem_variant<R, 0>(pass, kc.M, a, s);
+    else if (v == 1) launch_chem_variant<R, 1>(pass, kc.M, a, s);
+    else if (v == 2) launch_chem_variant<R, 2>(pass, kc.M, a, s);
+    else launch_chem_variant<R, 3>(pass, kc.M, a, s);
 }
 
 template <typename R>
@@ -726,60 +176,22 @@ hipError_t launch_chem(int part, bool fp32, const KGrid &g, const KChem &kc, con
                        const QueueView &q, int K, unsigned long long *hist, const SmoothArgs *sm, double a,
                        uint8_t *prev_att, DevStats *stats, hipStream_t s)
 {
-    if (fp32) {
-        ChemIO<float> io = make_io<float>(g.ncell, N, F, xHII, xHeII, xHeIII, T, nH, nacc, natt, nullptr, hist, sm, dt, a,
-                                          prev_att);
-        dispatch_SM<float, 0, 0>(part, g, kc, dk, dt, 0.f, 0.f, nullptr, nullptr, io, nullptr, 0, 0, q, K, stats, s);
-    } else {
-        ChemIO<double> io = make_io<double>(g.ncell, N, F, xHII, xHeII, xHeIII, T, nH, nacc, natt, nullptr, hist, sm, dt, a,
-                                            prev_att);
-        dispatch_SM<double, 0, 0>(part, g, kc, dk, dt, 0.0, 0.0, nullptr, nullptr, io, nullptr, 0, 0, q, K, stats, s);
-    }
+    const ChemPass pass = part == 1 ? CHEM_HEAD : CHEM_TAIL;
+    if (fp32)
+        launch_chem_pass<float>(pass, kc,
+                                {g, dk, dt, 0.f, 0.f, nullptr, nullptr,
+                                 make_io<float>(g.ncell, N, F, xHII, xHeII, xHeIII, T, nH, nacc, natt, nullptr, hist, sm,
+                                                dt, a, prev_att),
+                                 nullptr, 0, 0, q, K, stats, kc.isothermal != 0},
+                                s);
+    else
+        launch_chem_pass<double>(pass, kc,
+                                 {g, dk, dt, 0.0, 0.0, nullptr, nullptr,
+                                  make_io<double>(g.ncell, N, F, xHII, xHeII, xHeIII, T, nH, nacc, natt, nullptr, hist,
+                                                  sm, dt, a, prev_att),
+                                  nullptr, 0, 0, q, K, stats, kc.isothermal != 0},
+                                 s);
     return hipGetLastError();
-}
-
-// Positions a wave reserves at a time in the sweep: a quarter of a wave's
-// share of the grid, between one wave's width and CHEM_SWEEP_CHUNK (on a
-// small grid large reservations would leave the work to a few waves).
-static unsigned chem_sweep_chunk(size_t ncell)
-{
-    const size_t share = ncell / ((size_t)CHEM_ALL_BLOCKS * 4) / 4;
-    const size_t c = share < TAIL_CHUNK ? TAIL_CHUNK : (share > CHEM_SWEEP_CHUNK ? CHEM_SWEEP_CHUNK : share);
-    return (unsigned)c;
-}
-
-// one-pass chemistry: queue counters reset, the list of long chains, then
-// the persistent kernel
-template <typename R, int M, int V>
-static void launch_all(const KChem *dk, double dt, const ChemIO<R> &io, const QueueView &q, DevStats *st,
-                       hipStream_t s)
-{
-    hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(64), 0, s, q.count, 65);
-    if (io.prev_att && io.ncell > 0)
-        hipLaunchKernelGGL(k_long_list, dim3((unsigned)((io.ncell + 1023) / 1024)), dim3(256), 0, s, io.prev_att,
-                           io.ncell, q.cell, q.cap, q.cnt[0]);
-    hipLaunchKernelGGL((k_chem_all<R, M, V>), dim3(CHEM_ALL_BLOCKS), dim3(256), 0, s, dk, dt, io, q,
-                       chem_sweep_chunk(io.ncell), st);
-}
-
-template <typename R, int V>
-static void dispatch_all_M(const KChem &kc, const KChem *dk, double dt, const ChemIO<R> &io, const QueueView &q,
-                           DevStats *st, hipStream_t s)
-{
-    if (kc.M == 1) launch_all<R, 1, V>(dk, dt, io, q, st, s);
-    else if (kc.M == 2) launch_all<R, 2, V>(dk, dt, io, q, st, s);
-    else launch_all<R, 3, V>(dk, dt, io, q, st, s);
-}
-
-template <typename R>
-static void dispatch_all(const KChem &kc, const KChem *dk, double dt, const ChemIO<R> &io, const QueueView &q,
-                         DevStats *st, hipStream_t s)
-{
-    const int v = (io.sm.N ? V_SMOOTH : 0) | (kc.otsa ? 0 : V_CASE_A);
-    if (v == 0) dispatch_all_M<R, 0>(kc, dk, dt, io, q, st, s);
-    else if (v == 1) dispatch_all_M<R, 1>(kc, dk, dt, io, q, st, s);
-    else if (v == 2) dispatch_all_M<R, 2>(kc, dk, dt, io, q, st, s);
-    else dispatch_all_M<R, 3>(kc, dk, dt, io, q, st, s);
 }
 
 hipError_t launch_chem_all(bool fp32, const KGrid &g, const KChem &kc, const KChem *dk, double dt, void *N, void *F,
@@ -787,15 +199,20 @@ hipError_t launch_chem_all(bool fp32, const KGrid &g, const KChem &kc, const KCh
                            int32_t *natt, const QueueView &q, unsigned long long *hist, const SmoothArgs *sm, double a,
                            uint8_t *prev_att, DevStats *stats, hipStream_t s)
 {
-    if (fp32) {
-        ChemIO<float> io = make_io<float>(g.ncell, N, F, xHII, xHeII, xHeIII, T, nH, nacc, natt, nullptr, hist, sm, dt, a,
-                                          prev_att);
-        dispatch_all<float>(kc, dk, dt, io, q, stats, s);
-    } else {
-        ChemIO<double> io = make_io<double>(g.ncell, N, F, xHII, xHeII, xHeIII, T, nH, nacc, natt, nullptr, hist, sm, dt,
-                                            a, prev_att);
-        dispatch_all<double>(kc, dk, dt, io, q, stats, s);
-    }
+    if (fp32)
+        launch_chem_pass<float>(CHEM_ALL, kc,
+                                {g, dk, dt, 0.f, 0.f, nullptr, nullptr,
+                                 make_io<float>(g.ncell, N, F, xHII, xHeII, xHeIII, T, nH, nacc, natt, nullptr, hist, sm,
+                                                dt, a, prev_att),
+                                 nullptr, 0, 0, q, 0, stats, kc.isothermal != 0},
+                                s);
+    else
+        launch_chem_pass<double>(CHEM_ALL, kc,
+                                 {g, dk, dt, 0.0, 0.0, nullptr, nullptr,
+                                  make_io<double>(g.ncell, N, F, xHII, xHeII, xHeIII, T, nH, nacc, natt, nullptr, hist,
+                                                  sm, dt, a, prev_att),
+                                  nullptr, 0, 0, q, 0, stats, kc.isothermal != 0},
+                                 s);
     return hipGetLastError();
 }
 
@@ -808,21 +225,21 @@ hipError_t launch_step_fused(int part, bool fp32, int flux, const KGrid &g, cons
     // super-comoving transport: light speed a c_r over dt / a^2
     const double kdx = dt / (a * a) / g.dx;
     const double ctr = a * kc.cr;
-    if (fp32) {
-        ChemIO<float> io = make_io<float>(g.ncell, Nout, Fout, xHII, xHeII, xHeIII, T, nH, nacc, natt, acct, hist, sm, dt, a,
-                                          prev_att);
-        if (flux)
-            dispatch_SM<float, 1, 1>(part, g, kc, dk, dt, (float)ctr, (float)kdx, Nin, Fin, io, hll, nf, nth, q, K, stats, s);
-        else
-            dispatch_SM<float, 1, 0>(part, g, kc, dk, dt, (float)ctr, (float)kdx, Nin, Fin, io, hll, nf, nth, q, K, stats, s);
-    } else {
-        ChemIO<double> io = make_io<double>(g.ncell, Nout, Fout, xHII, xHeII, xHeIII, T, nH, nacc, natt, acct, hist, sm,
-                                            dt, a, prev_att);
-        if (flux)
-            dispatch_SM<double, 1, 1>(part, g, kc, dk, dt, ctr, kdx, Nin, Fin, io, hll, nf, nth, q, K, stats, s);
-        else
-            dispatch_SM<double, 1, 0>(part, g, kc, dk, dt, ctr, kdx, Nin, Fin, io, hll, nf, nth, q, K, stats, s);
-    }
+    const ChemPass pass = part == 2 ? CHEM_TAIL : (flux ? CHEM_FUSED_HLL : CHEM_FUSED_GLF);
+    if (fp32)
+        launch_chem_pass<float>(pass, kc,
+                                {g, dk, dt, (float)ctr, (float)kdx, (const float *)Nin, (const float *)Fin,
+                                 make_io<float>(g.ncell, Nout, Fout, xHII, xHeII, xHeIII, T, nH, nacc, natt, acct, hist,
+                                                sm, dt, a, prev_att),
+                                 (const float *)hll, nf, nth, q, K, stats, kc.isothermal != 0},
+                                s);
+    else
+        launch_chem_pass<double>(pass, kc,
+                                 {g, dk, dt, ctr, kdx, (const double *)Nin, (const double *)Fin,
+                                  make_io<double>(g.ncell, Nout, Fout, xHII, xHeII, xHeIII, T, nH, nacc, natt, acct,
+                                                  hist, sm, dt, a, prev_att),
+                                  (const double *)hll, nf, nth, q, K, stats, kc.isothermal != 0},
+                                 s);
     return hipGetLastError();
 }
 

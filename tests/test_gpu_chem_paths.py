@@ -12,7 +12,7 @@ import pytest
 import torch
 
 import rt_inputs as ri
-from test_gpu_parity import gas, make_pair, random_rad
+from test_gpu_parity import chem_compare, gas, make_pair, random_rad
 
 pytestmark = pytest.mark.gpu
 
@@ -137,3 +137,28 @@ def test_one_pass_refills_on_a_large_grid(fp32):
         b.step(dt, 1)
     s = compare(a, b)
     assert s["flags"] & 2
+
+
+@pytest.mark.parametrize("lo,hi", [(-2.0, 0.5), (0.9, 1.3), (7.2, 7.8), (7.5, 10.0)])
+def test_one_pass_at_the_ends_of_the_lds_rate_table(lo, hi):
+    # 10^lo .. 10^hi K: below, across and above the octaves (2^-3 K .. 2^25 K,
+    # the HeIII fits at a quarter) whose rates the persistent kernels read from
+    # LDS; the head pass reads all from global memory, so the bits must agree,
+    # and the oracle evaluates the formulas
+    rng = np.random.default_rng(int(10 * (hi + 20)))
+    n = (24, 17, 9)
+    N, F = random_rad(n, 3, rng)
+    gs = gas(n, rng)
+    gs["T"] = 10 ** rng.uniform(lo, hi, gs["T"].shape)
+    st = {"N": 1e-3 * N, "F": 1e-3 * F, **gs}
+    ctxs = []
+    for path in ("two-pass", "one-pass"):
+        ctx, o = make_pair(n, (0,) * 6, 3, 0)
+        ctx.set_chem_path(path)
+        ctx.load_state(st)
+        ctx.thermochem(ctx.courant_dt())
+        ctxs.append(ctx)
+    compare(*ctxs)
+    fl, nacc, natt = o.thermochem(st, ctxs[0].courant_dt(), want_counts=True)
+    st["nacc"], st["natt"] = nacc, natt
+    chem_compare(ctxs[1].state_numpy(), st)
