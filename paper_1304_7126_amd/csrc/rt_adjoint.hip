@@ -296,6 +296,8 @@ __global__ __launch_bounds__(256) void k_chem_record(const KChem *__restrict__ k
                                                      double *__restrict__ trace, DevStats *__restrict__ st)
 {
     const KChem &k = *kp;
+    __shared__ double rl[rate_table_len<0>()];
+    rate_table_to_lds<0>(k.rates, rl);
     const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= nc) return;
     const int cnt = counts[i];
@@ -322,7 +324,7 @@ __global__ __launch_bounds__(256) void k_chem_record(const KChem *__restrict__ k
         const double e5 = k.isothermal ? cc.Tiso : s.Tmu;
         const double h = s.h >= s.rem * (1.0 - 1e-10) ? s.rem : s.h;  // the length chem_attempt takes
         const int acc0 = s.acc;
-        done = chem_attempt<CM, 0, false, false>(k, k.rates, nullptr, cc, s, fl);  // one attempt per call: h above is its length
+        done = chem_attempt<CM, 0, false>(k, k.rates, rl, cc, s, fl);  // one attempt per call: h above is its length
         if (s.acc != acc0) {
             if (fits && n < cnt) {
                 double *e = tr + TV * n;
@@ -410,60 +412,124 @@ __global__ __launch_bounds__(256) void k_chem_replay(const KChem *__restrict__ k
 // --------------------------------------------------------------- chem adjoint
 // (lambda_N, lambda_F) after the chemistry -> (wN, wF) before it;
 // lambda_x, lambda_T in place; g_lnnH += the step's d/dln n_H.
-__global__ __launch_bounds__(256) void k_chem_adj(const KChem *__restrict__ kp, size_t nc,
-                                                  const double *__restrict__ nH, const int32_t *__restrict__ counts,
-                                                  const int64_t *__restrict__ off, long long cap,
-                                                  const double *__restrict__ trace, const double *__restrict__ lN,
-                                                  const double *__restrict__ lF, double *__restrict__ lx,
-                                                  double *__restrict__ lT, double *__restrict__ wN,
-                                                  double *__restrict__ wF, double *__restrict__ glnnH)
+//
+// A wave owns 64 cells, one per lane.  Only the products of the transposed
+// Jacobians are serial in a cell's substeps; the Jacobians themselves depend
+// on the recorded states alone.  So the wave works off its cells' substeps in
+// rounds: the m cells that have some left get q = 64 / m lanes each, every
+// lane linearises one substep (the last q of each cell), leaves the 20 numbers
+// the products need in LDS, and each cell's owner applies its q of them, last
+// first.  A wave with one cell of 160 substeps takes 3 rounds instead of 160
+// linearisations in a row; the chains at I-fronts used to set the kernel's
+// time (64^3, 16 sources, steps 11-20: 1,476 us per launch with one lane per
+// cell, 135 us so).
+constexpr int JV = 4 * ND + 4;  // d Nn, d xn, d Tmn, d rden, rden, F before the substep
+__global__ __launch_bounds__(64) void k_chem_adj(const KChem *__restrict__ kp, size_t nc,
+                                                 const double *__restrict__ nH, const int32_t *__restrict__ counts,
+                                                 const int64_t *__restrict__ off, long long cap,
+                                                 const double *__restrict__ trace, const double *__restrict__ lN,
+                                                 const double *__restrict__ lF, double *__restrict__ lx,
+                                                 double *__restrict__ lT, double *__restrict__ wN,
+                                                 double *__restrict__ wF, double *__restrict__ glnnH)
 {
+    __shared__ double jac[JV][64];
+    __shared__ int owner[64];
     const KChem &k = *kp;
-    const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= nc) return;
+    const int lane = threadIdx.x;
+    const size_t i = (size_t)blockIdx.x * 64 + lane;
+    const bool valid = i < nc;
     const bool iso = k.isothermal != 0;
-    const int cnt = counts[i];
-    const int64_t o = off[i];
-    double aN = lN[i], aFx = lF[i], aFy = lF[nc + i], aFz = lF[2 * nc + i], ax = lx[i], aT = lT[i];
-    double g = 0.0;
-    if (cnt >= 0 && o + cnt < (int64_t)cap) {
-        const double *tr = trace + (size_t)TV * (size_t)o;
-        const double *fin = tr + TV * cnt;
+    const int cnt = valid ? counts[i] : -1;
+    const int64_t o = valid ? off[i] : 0;
+    const bool fits = cnt >= 0 && o + cnt < (int64_t)cap;
+    double aN = 0.0, aFx = 0.0, aFy = 0.0, aFz = 0.0, ax = 0.0, aT = 0.0;
+    if (valid) {
+        aN = lN[i];
+        aFx = lF[i];
+        aFy = lF[nc + i];
+        aFz = lF[2 * nc + i];
+        ax = lx[i];
+        aT = lT[i];
+    }
+    double g = 0.0, lnnH = 0.0;
+    int left = 0;  // substeps not yet applied
+    if (fits) {
+        const double *fin = trace + (size_t)TV * (size_t)(o + cnt);
         const double nf = fin[6];  // substeps recorded, at most cnt
-        const int n = (nf >= 0.0 && nf <= (double)cnt) ? (int)nf : 0;
+        left = (nf >= 0.0 && nf <= (double)cnt) ? (int)nf : 0;
         if (!iso) {
             // T_out = T_mu mu(x), mu = 1/(X (1 + x))
             const double mu = 1.0 / (k.X * (1.0 + fin[4]));
             ax += aT * fin[5] * (-k.X * mu * mu);
             aT *= mu;
         }
-        const double lnnH = log(nH[i]);
-        for (int j = n - 1; j >= 0; --j) {
-            const double *e = tr + TV * j;
-            Dual Nn, xn, Tmn, rden;
-            dsubstep(k, e[6], dvar(e[0], VN), dvar(e[4], VX), dvar(e[5], VT), dvar(lnnH, VL), Nn, xn, Tmn, rden);
-            // F_out = F_in rden: the F adjoint scales, and (lambda_F . F_in) weighs d rden
-            const double wr = aFx * e[1] + aFy * e[2] + aFz * e[3];
-            double a[ND];
+        lnnH = log(nH[i]);
+    }
+    while (true) {
+        const unsigned long long m = __ballot(left > 0);
+        if (!m) break;
+        const int q = 64 / __popcll(m);
+        const int rank = __popcll(m & ((1ull << lane) - 1ull));
+        if (left > 0) owner[rank] = lane;
+        __syncthreads();
+        // linearise: lane a q + s takes substep left - 1 - s of cell a
+        {
+            const int a = lane / q, sub = lane - a * q;
+            const bool has = a < __popcll(m);
+            const int ow = has ? owner[a] : lane;
+            const int j = __shfl(left, ow, 64) - 1 - sub;
+            const int64_t oo = ((int64_t)__shfl((int)(o >> 32), ow, 64) << 32) | (uint32_t)__shfl((int)(uint32_t)o, ow, 64);
+            const double l = __shfl(lnnH, ow, 64);
+            if (has && j >= 0) {
+                const double *e = trace + (size_t)TV * (size_t)(oo + j);
+                Dual Nn, xn, Tmn, rden;
+                dsubstep(k, e[6], dvar(e[0], VN), dvar(e[4], VX), dvar(e[5], VT), dvar(l, VL), Nn, xn, Tmn, rden);
 #pragma unroll
-            for (int q = 0; q < ND; ++q)
-                a[q] = aN * Nn.d[q] + ax * xn.d[q] + (iso ? 0.0 : aT * Tmn.d[q]) + wr * rden.d[q];
-            aFx *= rden.v;
-            aFy *= rden.v;
-            aFz *= rden.v;
-            aN = a[VN];
-            ax = a[VX];
-            if (!iso) aT = a[VT];
-            g += a[VL];
+                for (int d = 0; d < ND; ++d) {
+                    jac[d][lane] = Nn.d[d];
+                    jac[ND + d][lane] = xn.d[d];
+                    jac[2 * ND + d][lane] = Tmn.d[d];
+                    jac[3 * ND + d][lane] = rden.d[d];
+                }
+                jac[4 * ND][lane] = rden.v;
+#pragma unroll
+                for (int d = 0; d < 3; ++d) jac[4 * ND + 1 + d][lane] = e[1 + d];
+            }
         }
-        if (!iso) {
-            // T_mu = T / mu(x) at the start of the chemistry
-            const double x0 = tr[4];
-            const double T0 = tr[5] / (k.X * (1.0 + x0));
-            const double aTm = aT;
-            aT = aTm * k.X * (1.0 + x0);
-            ax += aTm * T0 * k.X;
+        __syncthreads();
+        if (left > 0) {
+            const int n = left < q ? left : q;
+            for (int sub = 0; sub < n; ++sub) {
+                const int c = rank * q + sub;
+                // F_out = F_in rden: the F adjoint scales, and (lambda_F . F_in) weighs d rden
+                const double wr = aFx * jac[4 * ND + 1][c] + aFy * jac[4 * ND + 2][c] + aFz * jac[4 * ND + 3][c];
+                double a[ND];
+#pragma unroll
+                for (int d = 0; d < ND; ++d)
+                    a[d] = aN * jac[d][c] + ax * jac[ND + d][c] + (iso ? 0.0 : aT * jac[2 * ND + d][c]) +
+                           wr * jac[3 * ND + d][c];
+                const double rv = jac[4 * ND][c];
+                aFx *= rv;
+                aFy *= rv;
+                aFz *= rv;
+                aN = a[VN];
+                ax = a[VX];
+                if (!iso) aT = a[VT];
+                g += a[VL];
+            }
+            left -= n;
         }
+        __syncthreads();
+    }
+    if (!valid) return;
+    if (fits && !iso) {
+        // T_mu = T / mu(x) at the start of the chemistry
+        const double *tr = trace + (size_t)TV * (size_t)o;
+        const double x0 = tr[4];
+        const double T0 = tr[5] / (k.X * (1.0 + x0));
+        const double aTm = aT;
+        aT = aTm * k.X * (1.0 + x0);
+        ax += aTm * T0 * k.X;
     }
     wN[i] = aN;
     wF[i] = aFx;
@@ -694,7 +760,7 @@ hipError_t launch_chem_adj(const KChem *dk, size_t nc, const double *nH, const i
                            long long cap, const double *trace, const double *lN, const double *lF, double *lx,
                            double *lT, double *wN, double *wF, double *g, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_chem_adj, dim3((unsigned)((nc + 255) / 256)), dim3(256), 0, s, dk, nc, nH, counts, off, cap,
+    hipLaunchKernelGGL(k_chem_adj, dim3((unsigned)((nc + 63) / 64)), dim3(64), 0, s, dk, nc, nH, counts, off, cap,
                        trace, lN, lF, lx, lT, wN, wF, g);
     return hipGetLastError();
 }

@@ -271,3 +271,33 @@ def test_mixed_gradient_close_to_fp64_at_full_size():
     # measured: loss 9.2e-7, sources 3.1e-6 (each 2.5e-5), directions 7.3e-6
     assert e_L <= 1e-5
     assert e_src <= 1e-4 and e_src_each <= 1e-3 and e_dir <= 1e-4
+
+
+@pytest.mark.parametrize("n,srcs,iso", [(3, 1, False), (5, 2, True), (5, 3, False), (7, 20, False)])
+def test_gradient_of_partly_filled_waves(n, srcs, iso):
+    """The reverse chemistry hands a wave's 64 lanes to the cells that have
+    substeps left: cell counts that are no multiple of 64, one cell with a
+    long chain among cells with one substep, and many chains of different
+    lengths, against the oracle's complex-step derivative in every source and
+    one random density direction (the bound of the test above)."""
+    from paper_1304_7126_amd.adjoint import rt_run
+    w = ri.grey_box(n, 3.3 * n / 64, srcs, 6, seed=n, isothermal=iso)
+    run, ijk, nd, dt = make_run(w, every=4)
+    st, lnnd, lnnH = params(w, nd)
+    sN, sE, eb, _ = physics.spectrum_attributes(w.spectrum)
+    p = cs.CSParams(w.n, w.dx, w.c_r, sN[0][0], sE[0][0], eb[0], iso, X=w.X, gamma=w.gamma, a_exp=w.a_exp,
+                    x_min=w.x_min)
+    s0 = {"N": st["N"][0], "F": st["F"][0], "xHII": st["xHII"], "T": st["T"]}
+    target = torch.full((n,) * 3, 0.3, dtype=torch.float64, device="cuda")
+    a = lnnd.clone().requires_grad_(True)
+    b = lnnH.clone().requires_grad_(True)
+    loss = ((rt_run(run, a, b) - target) ** 2).sum()
+    loss.backward()
+    g_src, g_nH = a.grad.numpy(), b.grad.cpu().numpy()
+    scale = max(np.max(np.abs(g_src)), 1e-300)
+    rng = np.random.default_rng(n)
+    checks = [(np.eye(len(nd))[s], None) for s in range(len(nd))] + [(None, rng.standard_normal(g_nH.shape))]
+    for vs, vc in checks:
+        ref = cs.directional_derivative(p, s0, dt, w.steps, ijk, np.log(nd), np.log(st["nH"]), target.cpu().numpy(), vs, vc)
+        got = float(g_src @ vs) if vs is not None else float(np.sum(g_nH * vc))
+        assert abs(got - ref) <= 1e-8 * abs(ref) + 1e-12 * scale, (vs is not None, got, ref)
