@@ -227,6 +227,23 @@ static void build_hll(int nf, int nth, std::vector<double> &tab)
     }
 }
 
+namespace rtm1 {
+hipError_t upload_hll_table(bool fp32, const double *tab, int nf, int nth, void **out)
+{
+    const size_t n = (size_t)nf * nth;
+    std::vector<float> pairs;
+    std::vector<double> top;
+    if (fp32) pairs.assign(tab, tab + 2 * n);
+    else
+        for (size_t i = 0; i < n; ++i) top.push_back(tab[2 * i + 1]);
+    const size_t bytes = fp32 ? 2 * n * sizeof(float) : n * sizeof(double);
+    hipError_t e = hipMalloc(out, bytes);
+    if (e == hipSuccess)
+        e = hipMemcpy(*out, fp32 ? (const void *)pairs.data() : (const void *)top.data(), bytes, hipMemcpyHostToDevice);
+    return e;
+}
+}  // namespace rtm1
+
 // ---------------------------------------------------------------------------
 // Rate tables (rt_rates.h): built once per process and case (7 ms), copied
 // to every context's device.
@@ -471,17 +488,7 @@ extern "C" rt_status rt_init(const rt_grid *grid, const rt_groups *groups, const
 
     build_hll(c->nf, c->nth, c->hll_host);
     hipError_t e;
-    const size_t ntab = c->hll_host.size();
-    if (c->fp32) {
-        std::vector<float> tf(ntab);
-        for (size_t i = 0; i < ntab; ++i) tf[i] = (float)c->hll_host[i];
-        e = hipMalloc(&c->hll_dev, ntab * sizeof(float));
-        if (e == hipSuccess) e = hipMemcpy(c->hll_dev, tf.data(), ntab * sizeof(float), hipMemcpyHostToDevice);
-    } else {
-        e = hipMalloc(&c->hll_dev, ntab * sizeof(double));
-        if (e == hipSuccess)
-            e = hipMemcpy(c->hll_dev, c->hll_host.data(), ntab * sizeof(double), hipMemcpyHostToDevice);
-    }
+    e = upload_hll_table(c->fp32, c->hll_host.data(), c->nf, c->nth, &c->hll_dev);
     if (e == hipSuccess) e = hipMalloc((void **)&c->dstats, sizeof(DevStats));
     if (e == hipSuccess) e = hipMemset(c->dstats, 0, sizeof(DevStats));
     if (e == hipSuccess) e = hipMalloc((void **)&c->dred, sizeof(RedOut));

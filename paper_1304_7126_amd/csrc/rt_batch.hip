@@ -566,15 +566,7 @@ extern "C" rt_status rt_batch_init(int nbox, const rt_grid *grids, const rt_grou
     if (e == hipSuccess) e = hipMemcpy(b->dchunks, chunks.data(), chunks.size() * sizeof(Chunk), hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMalloc((void **)&b->dstats, sizeof(DevStats));
     if (e == hipSuccess) e = hipMemset(b->dstats, 0, sizeof(DevStats));
-    if (b->fp32) {
-        std::vector<float> tf(tab.size());
-        for (size_t i = 0; i < tab.size(); ++i) tf[i] = (float)tab[i];
-        if (e == hipSuccess) e = hipMalloc(&b->hll, tf.size() * sizeof(float));
-        if (e == hipSuccess) e = hipMemcpy(b->hll, tf.data(), tf.size() * sizeof(float), hipMemcpyHostToDevice);
-    } else {
-        if (e == hipSuccess) e = hipMalloc(&b->hll, tab.size() * sizeof(double));
-        if (e == hipSuccess) e = hipMemcpy(b->hll, tab.data(), tab.size() * sizeof(double), hipMemcpyHostToDevice);
-    }
+    if (e == hipSuccess) e = upload_hll_table(b->fp32, tab.data(), b->nf, b->nth, &b->hll);
     if (e != hipSuccess) {
         g_batch_err = std::string("device table allocation failed: ") + hipGetErrorString(e);
         rt_batch_free(b);

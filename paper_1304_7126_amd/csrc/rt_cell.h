@@ -128,7 +128,7 @@ __device__ __forceinline__ void face_flux(const U4<R> &L, const R PL[6], R lLm, 
         for (int m = 0; m < 4; ++m) Phi[m] = R(0.5) * (GL[m] + GR[m]);
         return;
     }
-    const R iden = rcp(den);
+    const R iden = rcp_ord(den);
 #pragma unroll
     for (int m = 0; m < 4; ++m) Phi[m] = (lp * GL[m] - lm * GR[m] + lp * lm * (uR[m] - uL[m])) * iden;
 }

@@ -55,6 +55,45 @@ __device__ __forceinline__ double div_pos(double a, double b)
     return fma(rem, r, q);
 }
 
+// The divisions, roots and angles of the transport whose arguments are
+// ordinary (neither zero nor overflowing): in FP32 the hardware reciprocal and
+// the library's root and arccos; in FP64 the reciprocal and the root from
+// the hardware's estimates and Newton steps (5 and 9 instructions where the
+// IEEE forms with their scaling and fix-ups take 11 and 18) and the angle of
+// rt_math.h.
+__device__ __forceinline__ float rcp_ord(float x) { return rcp(x); }
+__device__ __forceinline__ double rcp_ord(double x) { return rcp_pos(x); }
+__device__ __forceinline__ float sqrt_ord(float x) { return sqrt(x); }
+__device__ __forceinline__ double sqrt_ord(double x)
+{
+    // the Goldschmidt steps of sqrt_and_inv; zero (and what underflows in the
+    // square) stays zero
+    const double r = __builtin_amdgcn_rsq(fmax(x, 1e-300));
+    double g = x * r, h = 0.5 * r;
+    const double e = fma(-g, h, 0.5);
+    g = fma(g, e, g);
+    h = fma(h, e, h);
+    return fma(fma(-g, g, x), h, g);
+}
+// 1/sqrt(x)
+__device__ __forceinline__ float rsqrt_ord(float x) { return 1.0f / sqrt(x); }
+__device__ __forceinline__ double rsqrt_ord(double x)
+{
+    double r = __builtin_amdgcn_rsq(x);
+    double e = fma(-x * r, r, 1.0);
+    r = fma(0.5 * r, e, r);
+    e = fma(-x * r, r, 1.0);
+    return fma(0.5 * r, e, r);
+}
+// the angle of cosine c, whose other two direction components are u and v
+// (FP32: from the cosine alone)
+__device__ __forceinline__ float angle_of(float c, float, float) { return acos(c); }
+__device__ __forceinline__ double angle_of(double c, double u, double v)
+{
+    return angle_by(
+        c, u * u + v * v, [](double z) { return sqrt_ord(z); }, [](double x) { return rcp_pos(x); });
+}
+
 // ---------------------------------------------------------------------
 // M1 pressure flux.  For a cell state U = (N, F) the physical flux along
 // axis d is G_d = (F_d, c^2 P_d.), P = N D with
@@ -83,12 +122,12 @@ __device__ __forceinline__ void m1_pressure(R N, R Fx, R Fy, R Fz, R c, R P[6])
     const R ax = Fx * icN, ay = Fy * icN, az = Fz * icN;
     const R sr = ax * ax + ay * ay + az * az;
     const R s = sr > R(1) ? R(1) : sr;
-    const R r = sqrt(R(4) - R(3) * s);
-    const R inv = rcp(R(5) + R(2) * r);
+    const R r = sqrt_ord(R(4) - R(3) * s);
+    const R inv = rcp_ord(R(5) + R(2) * r);
     const R chi = (R(3) + R(4) * s) * inv;
     const R c2N = c * cN;
     const R iso = R(0.5) * (R(1) - chi) * c2N;
-    const R B = (sr > R(1) ? rcp(sr) : (R(3) * rcp(R(2) + r) + R(6)) * inv) * c2N;
+    const R B = (sr > R(1) ? rcp(sr) : (R(3) * rcp_ord(R(2) + r) + R(6)) * inv) * c2N;
     P[0] = iso + B * ax * ax;
     P[1] = iso + B * ay * ay;
     P[2] = iso + B * az * az;
@@ -115,7 +154,7 @@ __device__ __forceinline__ void limit_flux(R &N, R &Fx, R &Fy, R &Fz, R c)
     const R ax = Fx * icN, ay = Fy * icN, az = Fz * icN;
     const R a2 = ax * ax + ay * ay + az * az;
     if (a2 > R(1)) {
-        const R s = R(1) / sqrt(a2);
+        const R s = a2 < R(1e30) ? rsqrt_ord(a2) : R(1) / sqrt(a2);
         Fx *= s;
         Fy *= s;
         Fz *= s;
@@ -143,6 +182,9 @@ __device__ __forceinline__ void prow(const R P[6], int d, R &px, R &py, R &pz)
 // ---------------------------------------------------------------------
 // The part of the lookup shared by the three axes: the table row (f) and,
 // per axis, ct_d = num_d * q (or 1 where the cell has no flux direction).
+// These keep the IEEE root and divisions in FP64 too: next to f = 1 and an
+// angle of pi/2 both speeds are near zero and the HLL weights magnify an ulp
+// of f or of the direction a thousandfold.
 template <typename R>
 struct HllPrep {
     R num[3];
@@ -196,18 +238,27 @@ __device__ __forceinline__ void hll_axis(const R *__restrict__ tab, int nth, con
 {
     R ct = p.dir ? p.num[d] * p.q : R(1);
     ct = ct > R(1) ? R(1) : (ct < R(-1) ? R(-1) : ct);
-    const R th = acos(ct);
+    const R th = angle_of(ct, p.num[d == 0 ? 1 : 0] * p.q, p.num[d == 2 ? 1 : 2] * p.q);
     const R ut = th * R(0.31830988618379067154) * R(nth - 1);
     int k = (int)floor(ut);
     k = k > nth - 2 ? nth - 2 : (k < 0 ? 0 : k);
     const R wf = p.wf, wt = ut - R(k);
-    const R *t00 = tab + ((size_t)p.i * nth + k) * 2;
-    const R *t01 = t00 + 2;
-    const R *t10 = t00 + (size_t)nth * 2;
-    const R *t11 = t10 + 2;
     const R a00 = (R(1) - wf) * (R(1) - wt), a10 = wf * (R(1) - wt), a01 = (R(1) - wf) * wt, a11 = wf * wt;
-    lmin = a00 * t00[0] + a10 * t10[0] + a01 * t01[0] + a11 * t11[0];
-    lmax = a00 * t00[1] + a10 * t10[1] + a01 * t01[1] + a11 * t11[1];
+    if constexpr (sizeof(R) == 8) {
+        // the FP64 device table holds lambda_max only: lambda_min(f, theta) =
+        // -lambda_max(f, pi - theta), whose nodes mirror (hll_device_table)
+        const R *t0 = tab + p.i * nth, *t1 = t0 + nth;
+        const int j = nth - 2 - k;
+        lmax = a00 * t0[k] + a10 * t1[k] + a01 * t0[k + 1] + a11 * t1[k + 1];
+        lmin = -(a00 * t0[j + 1] + a10 * t1[j + 1] + a01 * t0[j] + a11 * t1[j]);
+    } else {
+        const R *t00 = tab + ((size_t)p.i * nth + k) * 2;
+        const R *t01 = t00 + 2;
+        const R *t10 = t00 + (size_t)nth * 2;
+        const R *t11 = t10 + 2;
+        lmin = a00 * t00[0] + a10 * t10[0] + a01 * t01[0] + a11 * t11[0];
+        lmax = a00 * t00[1] + a10 * t10[1] + a01 * t01[1] + a11 * t11[1];
+    }
     const R a = p.f * ct;
     lmin = lmin < a ? lmin : a;
     lmax = lmax > a ? lmax : a;

@@ -212,6 +212,11 @@ inline void kchem_derive(KChem &k)
         }
 }
 
+// HLL wave speeds for the device (freed with hipFree) from the host table
+// [f][theta][lambda_min, lambda_max]: the pairs in FP32; in FP64 lambda_max
+// alone, [f][theta] (lambda_min is its mirror image): half the gathers' bytes
+hipError_t upload_hll_table(bool fp32, const double *tab, int nf, int nth, void **out);
+
 // device copy of the rate table of the case in use (freed with hipFree); the
 // host tables are built on first use and kept (0.7 MB)
 hipError_t upload_rate_table(bool otsa, double **out);

@@ -211,7 +211,12 @@ __device__ __forceinline__ void block_sum2(double a, double b, double &sa, doubl
 // is copied into LDS when the block starts, so that the twelve bilinear
 // corner reads of a cell (three axes) and those of the halo rows are LDS
 // reads instead of L2 gathers; with the single record buffer it fits the
-// 160 KiB a workgroup may hold.
+// 160 KiB a workgroup may hold.  In FP64 it stays in global memory, lambda_max
+// alone (81.6 KB; lambda_min is its mirror image): in LDS it would have to
+// share the records' place with the fluxes, and the two more barriers per
+// plane cost more than the gathers (256^3 x 3: 2.68 against 2.51 ms; now
+// 2.58, with pairs in global memory, IEEE divisions and roots throughout and
+// the library's arccos 2.85).
 constexpr int LTAB_CAP = 101 * 101 * 2;
 template <typename R, int FLUX, int NT, bool AHEAD>
 __global__ __launch_bounds__(NT) void k_transport_z(KGrid g, int H, int zc, R c, R kdx, const R *__restrict__ Nin,
