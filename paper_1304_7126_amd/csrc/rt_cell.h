@@ -591,10 +591,10 @@ constexpr int QV_SMOOTH = QV_GRID + 6;
 #define RT_TAIL_CHUNK 64
 #endif
 constexpr unsigned TAIL_CHUNK = RT_TAIL_CHUNK;
-// the most positions a wave of the one-pass chemistry reserves at a time
-// once past the long chains (measured at 256^3 x 3: 64 -> 4.73 ms, 128 ->
-// 4.30, 256 -> 4.27, 512 -> 4.29, 1024 -> 5.54 ms, the last from the
-// imbalance at the end); smaller grids take less (chem_sweep_chunk)
+// positions a wave of the one-pass chemistry reserves at a time where all
+// waves share one counter on a large grid, in grid order (256^3 x 3: 64 ->
+// 4.73 ms, 128 -> 4.30, 256 -> 4.27, 512 -> 4.29, 1024 -> 5.54 ms, the last
+// from the imbalance at the end)
 #ifndef RT_CHEM_SWEEP_CHUNK
 #define RT_CHEM_SWEEP_CHUNK 256
 #endif
@@ -688,10 +688,8 @@ __device__ __forceinline__ R finish_flux(const ChemIO<R> &io, const S &s, int g,
         return (R)((double)fp * s.fs[g]);
 }
 
-// The previous-pass attempt count kept per cell: the count, capped at 127,
-// in bits 0-6; bit 7 marks a cell the chemistry pass takes from its list of
-// long chains (it is then passed over in the sweep over all cells).
-constexpr uint8_t ATT_MASK = 0x7F, ATT_LISTED = 0x80;
+// The previous-pass attempt count kept per cell is capped at this.
+constexpr int ATT_CAP = 127;
 
 // Write a finished cell: N, the flux in the destination scaled by fs (with
 // smoothed RT: fs F^t + fb (F' - F^t)/dt_RT), the gas state and the counters.
@@ -701,7 +699,7 @@ constexpr uint8_t ATT_MASK = 0x7F, ATT_LISTED = 0x80;
 // stores would each wait out the stores before them.
 template <typename R, int M, bool LOADED, class S>
 __device__ __forceinline__ void store_cell_impl(const ChemIO<R> &io, uint32_t i, const S &s, double T,
-                                                const R *fpin, uint8_t mark)
+                                                const R *fpin)
 {
     constexpr bool SM = S::smooth;
     const size_t nc = io.ncell;
@@ -721,7 +719,7 @@ __device__ __forceinline__ void store_cell_impl(const ChemIO<R> &io, uint32_t i,
     io.T[i] = T;
     if (io.nacc) io.nacc[i] = s.acc;
     if (io.natt) io.natt[i] = s.att;
-    if (io.prev_att) io.prev_att[i] = (uint8_t)(mark | (s.att < (int)ATT_MASK ? s.att : (int)ATT_MASK));
+    if (io.prev_att) io.prev_att[i] = (uint8_t)(s.att < ATT_CAP ? s.att : ATT_CAP);
 #pragma unroll
     for (int g = 0; g < M; ++g)
 #pragma unroll
@@ -729,17 +727,16 @@ __device__ __forceinline__ void store_cell_impl(const ChemIO<R> &io, uint32_t i,
 }
 
 template <typename R, int M, class S>
-__device__ __forceinline__ void store_cell(const ChemIO<R> &io, uint32_t i, const S &s, double T, uint8_t mark = 0)
+__device__ __forceinline__ void store_cell(const ChemIO<R> &io, uint32_t i, const S &s, double T)
 {
-    store_cell_impl<R, M, false>(io, i, s, T, nullptr, mark);
+    store_cell_impl<R, M, false>(io, i, s, T, nullptr);
 }
 
 // the same with the destination fluxes loaded by the caller
 template <typename R, int M, class S>
-__device__ __forceinline__ void store_cell_with(const ChemIO<R> &io, uint32_t i, const S &s, double T, const R *fp,
-                                                uint8_t mark = 0)
+__device__ __forceinline__ void store_cell_with(const ChemIO<R> &io, uint32_t i, const S &s, double T, const R *fp)
 {
-    store_cell_impl<R, M, true>(io, i, s, T, fp, mark);
+    store_cell_impl<R, M, true>(io, i, s, T, fp);
 }
 
 }  // namespace rtm1

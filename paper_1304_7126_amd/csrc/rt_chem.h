@@ -16,6 +16,7 @@ namespace rtm1 {
 constexpr int CHEM_WAVES = RT_CHEM_WAVES;
 constexpr int CHEM_THREADS = CHEM_WAVES * 256;
 constexpr int CHEM_BLOCKS = 256;
+constexpr unsigned CHEM_XCDS = 8;
 
 enum ChemPass { CHEM_HEAD, CHEM_FUSED_GLF, CHEM_FUSED_HLL, CHEM_TAIL, CHEM_ALL };
 

@@ -163,7 +163,7 @@ __global__ __launch_bounds__(256, (head_waves<R, M>())) void k_head(KGrid g, con
     // longest chains start first instead of draining the tail at its end.
     const bool want = !done;
     const int cls = !want ? 3
-                          : (io.prev_att && (io.prev_att[i] & ATT_MASK) >= TAIL_LONG_ATTEMPTS) ? 0
+                          : (io.prev_att && io.prev_att[i] >= TAIL_LONG_ATTEMPTS) ? 0
                                                                                                  : (s.acc == 0 ? 1 : 2);
     unsigned p = ~0u;
 #pragma unroll
@@ -301,100 +301,107 @@ static __global__ void k_zero_u32(unsigned *p, int n)
     for (int k = threadIdx.x; k < n; k += blockDim.x) p[k] = 0u;
 }
 
-// Before the one-pass chemistry, cells go to three lists (regions of the
-// queue's cell array) that the pass takes before it sweeps over the rest:
-//   0  the previous pass took at least TAIL_LONG_ATTEMPTS attempts, cold gas
-//   1  the same, warm gas
-//   2  the other cells of warm gas (above T_COLD_COOL)
-// Long chains first, so that they do not start late and drain the chip at
-// the end; warm and cold gas apart, so that the waves of cold gas skip the
-// Boltzmann factors, which take more than half of an attempt's instructions
-// and which one warm lane makes its whole wave execute (256^3 x 3 groups with
-// 200 bubbles, every wave mixed: 650 VALU instructions per trip and wave
-// where cold gas needs 300).  T null: the gas is one class (isothermal).
-// Listed cells are marked ATT_LISTED; what a region has no room for stays in
-// the sweep.  A block takes 4,096 cells, four consecutive ones per thread
-// (one 4-byte word of counts; the array is padded to 256 bytes), and adds to
-// each counter once.
-constexpr int ORDER_THREADS = 1024;
-static __global__ __launch_bounds__(ORDER_THREADS) void k_order(uint8_t *__restrict__ prev, const double *__restrict__ T,
-                                                                size_t nc, QueueView q)
+// The order in which the one-pass chemistry takes the cells.  Each block
+// sorts the ORDER_CELLS cells of its piece of the grid by what their attempts
+// will cost and how many they will be,
+//   the temperature, by the thresholds above which an attempt evaluates
+//   Boltzmann factors (a lane above one makes its whole wave execute them:
+//   650 VALU instructions per trip where cold gas needs 300),
+//   then the attempts of the previous pass (the state moves little in a step),
+// so that the lanes of a wave run the same code and end together, and their
+// next cells are neighbours again: the loads and stores of 64 cells then
+// take one set of memory instructions instead of three or four.  Sorted
+// pieces, not a sorted grid: one pass over T, and neighbours stay together.
+// Measured with the slabs of k_chem_all, against three lists over the whole
+// grid (us per step): 97 x 61 x 45 273 -> 222, 64^3 355 -> 304, shadowed 128^3
+// 810 -> 750, smoothed 128^3 558 -> 520, 256^3 x 3 3,980 -> 3,765; pieces of
+// 2,048 and 8,192 cells and half the keys are within 2% of that.  Sorted
+// pieces without the slabs: 256^3 x 3 4,015 and 3 times the bytes fetched.
+// Cells that took at least TAIL_LONG_ATTEMPTS go to two lists (cold gas in
+// q.acc, warm gas in q.att) that the pass takes first, so that the longest
+// chains do not start late and drain the chip at the end; -1 fills their
+// places.  T null: the gas is one class (isothermal).
+constexpr int ORDER_THREADS = 512, ORDER_CELLS = 4096, ORDER_PER = ORDER_CELLS / ORDER_THREADS;
+constexpr int ORDER_KEYS = 32;
+static __device__ __forceinline__ int order_bin(unsigned att)
 {
-    const size_t w = (size_t)blockIdx.x * ORDER_THREADS + threadIdx.x;  // word index
-    const size_t i0 = 4 * w;
-    uint32_t o = 0;
-    double Tc[4] = {0.0, 0.0, 0.0, 0.0};
-    if (i0 < nc) {
-        o = reinterpret_cast<const uint32_t *>(prev)[w];
-        if (T) {
+    return att <= 4u ? (att ? (int)att - 1 : 0) : att <= 6u ? 4 : att <= 8u ? 5 : att <= 12u ? 6 : 7;
+}
+static __global__ __launch_bounds__(ORDER_THREADS) void k_order(const uint8_t *__restrict__ prev,
+                                                                const double *__restrict__ T, size_t nc, QueueView q)
+{
+    // per key: its cells, then where its run starts; the last two: the lists
+    __shared__ unsigned cnt[ORDER_KEYS + 2], beg[ORDER_KEYS + 2];
+    __shared__ uint16_t place[ORDER_CELLS];
+    const size_t c0 = (size_t)blockIdx.x * ORDER_CELLS;
+    const unsigned nhere = nc - c0 < (size_t)ORDER_CELLS ? (unsigned)(nc - c0) : (unsigned)ORDER_CELLS;
+    if (threadIdx.x < ORDER_KEYS + 2) cnt[threadIdx.x] = 0u;
+    if (blockIdx.x == 0 && threadIdx.x < CHEM_XCDS) q.slab[threadIdx.x * QUEUE_SLAB_STRIDE] = 0u;
+    unsigned att[ORDER_PER];
+    double Tc[ORDER_PER];
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
-                if (i0 + j < nc) Tc[j] = T[i0 + j];
-        }
-    }
-    int cls[4];  // 0..2: the list, 3: none
-    unsigned long long c = 0;  // the thread's cells per list, 20 bits each
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const bool lng = ((o >> (8 * j)) & ATT_MASK) >= (unsigned)TAIL_LONG_ATTEMPTS;
-        const bool warm = Tc[j] > T_COLD_COOL;
-        cls[j] = i0 + j >= nc ? 3 : (lng ? (warm ? 1 : 0) : (warm ? 2 : 3));
-        if (cls[j] < 3) c += 1ull << (20 * cls[j]);
-    }
-    // exclusive sums over the wave, then over the block's waves
-    unsigned long long ex = c;
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const unsigned long long u = __shfl_up(ex, d, 64);
-        if (lane_id() >= d) ex += u;
-    }
-    __shared__ unsigned long long wsum[ORDER_THREADS / 64];
-    __shared__ unsigned base[3];
-    if (lane_id() == 63) wsum[threadIdx.x >> 6] = ex;
-    __syncthreads();
-    unsigned long long before = 0, tot = 0;
-#pragma unroll
-    for (int k = 0; k < ORDER_THREADS / 64; ++k) {
-        if (k < (int)(threadIdx.x >> 6)) before += wsum[k];
-        tot += wsum[k];
-    }
-    if (threadIdx.x < 3) {
-        const unsigned n = (unsigned)(tot >> (20 * threadIdx.x)) & 0xFFFFFu;
-        if (n) base[threadIdx.x] = atomicAdd(q.cnt[threadIdx.x], n);
+    for (int j = 0; j < ORDER_PER; ++j) {
+        const unsigned l = threadIdx.x + j * ORDER_THREADS;
+        att[j] = l < nhere ? (unsigned)prev[c0 + l] : 0u;
+        Tc[j] = T && l < nhere ? T[c0 + l] : 0.0;
     }
     __syncthreads();
-    ex = before + ex - c;
-    uint32_t nw = 0;
+    int key[ORDER_PER];
+    unsigned rank[ORDER_PER];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        uint32_t b = (o >> (8 * j)) & ATT_MASK;
-        if (cls[j] < 3) {
-            const unsigned k = base[cls[j]] + ((unsigned)(ex >> (20 * cls[j])) & 0xFFFFFu);
-            ex += 1ull << (20 * cls[j]);
-            if (k < q.rlen[cls[j]]) {
-                q.cell[q.rbeg[cls[j]] + k] = (int32_t)(i0 + j);
-                b |= ATT_LISTED;
-            }
-        }
-        nw |= b << (8 * j);
+    for (int j = 0; j < ORDER_PER; ++j) {
+        const int cls = !(Tc[j] > T_COLD_COOL) ? 0 : Tc[j] <= T_COLD_HI ? 1 : Tc[j] <= T_COLD_HEII ? 2 : 3;
+        // (no count yet, a state just set: warm gas may have long chains)
+        const bool lng = att[j] >= (unsigned)TAIL_LONG_ATTEMPTS || (att[j] == 0u && cls);
+        key[j] = lng ? ORDER_KEYS + (cls ? 1 : 0) : 8 * cls + order_bin(att[j]);
+        rank[j] = threadIdx.x + j * ORDER_THREADS < nhere ? atomicAdd(&cnt[key[j]], 1u) : 0u;
     }
-    if (i0 < nc && nw != o) reinterpret_cast<uint32_t *>(prev)[w] = nw;
+    __syncthreads();
+    if (threadIdx.x < ORDER_KEYS) {
+        unsigned s = cnt[threadIdx.x];
+#pragma unroll
+        for (int d = 1; d < ORDER_KEYS; d <<= 1) {
+            const unsigned u = __shfl_up(s, d, 64);
+            if ((int)threadIdx.x >= d) s += u;
+        }
+        beg[threadIdx.x] = s - cnt[threadIdx.x];
+    } else if (threadIdx.x < ORDER_KEYS + 2) {
+        const unsigned n = cnt[threadIdx.x];
+        beg[threadIdx.x] = n ? atomicAdd(q.cnt[threadIdx.x - ORDER_KEYS], n) : 0u;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < ORDER_PER; ++j) {
+        const unsigned l = threadIdx.x + j * ORDER_THREADS;
+        if (l >= nhere) continue;
+        const unsigned p = beg[key[j]] + rank[j];
+        if (key[j] < ORDER_KEYS) place[p] = (uint16_t)l;
+        else (key[j] == ORDER_KEYS ? q.acc : q.att)[p] = (int32_t)(c0 + l);
+    }
+    __syncthreads();
+    const unsigned n = beg[ORDER_KEYS - 1] + cnt[ORDER_KEYS - 1];
+#pragma unroll
+    for (int j = 0; j < ORDER_PER; ++j) {
+        const unsigned l = threadIdx.x + j * ORDER_THREADS;
+        if (l < nhere) q.cell[c0 + l] = l < n ? (int32_t)(c0 + place[l]) : -1;
+    }
 }
 
 // The chemistry of every cell in one persistent launch (the pass after a
 // separate transport): each lane takes a cell, runs its attempts one per
 // loop trip (an attempt that fails the photon check repeats at once with the
 // halved substep), writes it when it has filled dt_RT and takes the next,
-// from its wave's reservation of positions.  Positions run over the lists of
-// k_order (the waves of long chains issue ahead of the others), then over all
-// cells in grid order, passing over the listed ones.  Every cell goes
+// from its wave's reservation of positions.  With ordered, positions run over
+// the lists of k_order (the waves of long chains issue ahead of the others),
+// then over its sorted pieces; otherwise over the grid.  Every cell goes
 // through the same attempt code as in the head and tail passes, so results
 // are those of the two-pass chemistry bit for bit; what changes is that a
 // lane whose cell is done no longer idles until its wave's other lanes are.
 template <typename R, int M, int V>
 __global__ __launch_bounds__(CHEM_THREADS, CHEM_WAVES) void k_chem_all(const KChem *__restrict__ kp, double dt,
                                                                             ChemIO<R> io, QueueView q,
-                                                                            unsigned sweep_chunk,
+                                                                            bool ordered, unsigned slabs, unsigned piece,
+                                                                            unsigned chunk,
                                                                             DevStats *__restrict__ st)
 {
     const KChem &k = *kp;
@@ -402,25 +409,67 @@ __global__ __launch_bounds__(CHEM_THREADS, CHEM_WAVES) void k_chem_all(const KCh
     rate_table_to_lds<V>(k.rates, rt);
     constexpr bool SM = (V & V_SMOOTH) != 0;
     const size_t nc = io.ncell;
-    // the lists of k_order: positions below n0 and n1 are long chains, below nl listed
-    const unsigned n0 = io.prev_att ? min(*q.cnt[0], q.rlen[0]) : 0u;
-    const unsigned n1 = n0 + (io.prev_att ? min(*q.cnt[1], q.rlen[1]) : 0u);
-    const unsigned nl = n1 + (io.prev_att ? min(*q.cnt[2], q.rlen[2]) : 0u);
-    const unsigned n = nl + (unsigned)nc;
+    // positions below n0 and n1: the lists of long chains
+    const unsigned n0 = ordered ? *q.cnt[0] : 0u;
+    const unsigned n1 = n0 + (ordered ? *q.cnt[1] : 0u);
     ChemState<V> s;
     // the cell's destination fluxes, loaded with the cell (not with smoothed
     // RT, which has two sets of them)
     constexpr bool PRE = !SM;
     R fpre[PRE ? 3 * M : 1];
     uint32_t cell = 0;
-    CC cc{1.0, 0.0, 0.0, 0.0};
+    CC cc{1.0, 0.0, 0.0, 10.0};
     bool active = false, exhausted = false, raised = false;
-    uint8_t mark = 0;
-    // positions this wave has reserved and not yet handed out: the first
-    // wave's width without an atomic, dealt out block by block so that a small
-    // grid's waves spread over all CUs; the shared counter starts after those
-    const unsigned first0 = gridDim.x * (blockDim.x >> 6) * 64u;
-    unsigned rbase = ((threadIdx.x >> 6) * gridDim.x + blockIdx.x) * 64u, ravail = 64u;
+    // Positions this wave has reserved and not yet handed out: below n1 the
+    // lists, from there the cells.  A wave takes its share of the lists, then
+    // the cells of its XCD's slab (every eighth piece of the grid; workgroup b
+    // is on XCD b % 8), so that the lines of a piece are read by one L2 only,
+    // then what is left of the other slabs.  The first wave's width of each
+    // needs no atomic, and is dealt out block by block so that a small grid's
+    // waves spread over all CUs.
+    const unsigned waves = blockDim.x >> 6, wave = threadIdx.x >> 6;
+    const unsigned first0 = gridDim.x * waves * 64u;
+    const unsigned npiece = ((unsigned)nc + piece - 1u) / piece;
+    unsigned slab = blockIdx.x % slabs, left = slabs;
+    unsigned rbase = (wave * gridDim.x + blockIdx.x) * 64u;
+    unsigned ravail = rbase < n1 ? min(64u, n1 - rbase) : 0u;
+    bool lists = n1 > first0, own = true;
+    auto reserve = [&]() {
+        ravail = 0u;
+        if (lists) {
+            unsigned at = 0;
+            if (lane_id() == 0) at = atomicAdd(q.head, 64u);
+            at = first0 + (unsigned)__builtin_amdgcn_readfirstlane(at);
+            if (at < n1) {
+                rbase = at;
+                ravail = min(64u, n1 - at);
+                return;
+            }
+            lists = false;
+        }
+        while (!exhausted) {
+            // positions in the slab: the first widths of its waves, then by its counter
+            const unsigned nb = (gridDim.x - slab + slabs - 1u) / slabs;
+            unsigned at = nb * waves * 64u, take = 64u;
+            if (own) {
+                own = false;
+                at = (wave * nb + blockIdx.x / slabs) * 64u;
+            } else if (at / piece * slabs + slab < npiece) {
+                unsigned got = 0;
+                if (lane_id() == 0) got = atomicAdd(q.slab + slab * QUEUE_SLAB_STRIDE, chunk);
+                at += (unsigned)__builtin_amdgcn_readfirstlane(got);
+                take = chunk;
+            }
+            const unsigned pc = at / piece * slabs + slab;
+            if (pc < npiece) {
+                rbase = n1 + pc * piece + at % piece;
+                ravail = take;
+                return;
+            }
+            slab = (slab + 1u) % slabs;
+            exhausted = --left == 0u;
+        }
+    };
     unsigned fl = 0, cfl = 0;        // flags of the lane, flags of its current cell
     unsigned a_acc = 0, a_att = 0, a_max = 0;  // of this lane's cells (32 bits outlast a lane's work)
     __shared__ unsigned s_hist[64];
@@ -476,13 +525,22 @@ __global__ __launch_bounds__(CHEM_THREADS, CHEM_WAVES) void k_chem_all(const KCh
         }
         fl |= cfl;
         const double T = chem_finish<CM>(k, cc, s, fl);
-        if constexpr (PRE) store_cell_with<R, M>(io, cell, s, T, fpre, mark);
-        else store_cell<R, M>(io, cell, s, T, mark);
+        if constexpr (PRE) store_cell_with<R, M>(io, cell, s, T, fpre);
+        else store_cell<R, M>(io, cell, s, T);
         if (io.hist) hist_add(s_hist, s.acc);
         a_acc += (unsigned)s.acc;
         a_att += (unsigned)s.att;
         a_max = a_max > (unsigned)s.att ? a_max : (unsigned)s.att;
     };
+    // what a lane without a cell holds: an attempt on it ends at the photon
+    // stage's cap, in cold gas
+    auto idle = [&]() {
+        s.att = k.max_att32;
+        s.x = 0.5;
+        s.y2 = s.y3 = 0.25;
+        s.Tmu = 10.0;
+    };
+    idle();
     while (true) {
         if (!exhausted) {
             bool first = false;
@@ -491,40 +549,33 @@ __global__ __launch_bounds__(CHEM_THREADS, CHEM_WAVES) void k_chem_all(const KCh
             if (m) {
                 const unsigned nneed = (unsigned)__popcll(m);
                 const unsigned r = (unsigned)__popcll(m & ((1ull << lane_id()) - 1ull));
-                unsigned t;
+                unsigned t = rbase + r;
+                bool got = need && r < ravail;
                 if (ravail >= nneed) {
-                    t = rbase + r;
                     rbase += nneed;
                     ravail -= nneed;
                 } else {
-                    // one wave's width at a time among the long chains, so
-                    // that a wave does not hold a second set of them; more
-                    // in the sweep (sweep_chunk), where each reservation is
-                    // an atomic on the one counter every wave shares
-                    const unsigned more = nneed - ravail;
-                    const unsigned chunk = rbase < n1 ? TAIL_CHUNK : sweep_chunk;
-                    const unsigned take = more > chunk ? more : chunk;
-                    const int leader = __ffsll((long long)m) - 1;
-                    unsigned base = 0;
-                    if (lane_id() == leader) base = first0 + atomicAdd(q.head, take);
-                    base = __shfl(base, leader);
-                    t = r < ravail ? rbase + r : base + (r - ravail);
-                    rbase = base + more;
-                    ravail = take - more;
-                }
-                if (rbase >= n) exhausted = true;
-                if (need && t < n) {
-                    bool take = true;
-                    if (t < nl) {
-                        cell = (uint32_t)q.cell[t < n0 ? t : (t < n1 ? q.rbeg[1] + (t - n0) : q.rbeg[2] + (t - n1))];
-                        mark = ATT_LISTED;
-                        first = t < n1;
-                    } else {
-                        cell = t - nl;
-                        mark = 0;
-                        take = !io.prev_att || !(io.prev_att[cell] & ATT_LISTED);
+                    // what is left of the reservation goes first
+                    const unsigned had = ravail, more = nneed - ravail;
+                    reserve();
+                    if (need && r >= had && r - had < ravail) {
+                        t = rbase + (r - had);
+                        got = true;
                     }
-                    if (take) {
+                    const unsigned used = min(more, ravail);
+                    rbase += used;
+                    ravail -= used;
+                }
+                got = got && t < n1 + (unsigned)nc;
+                if (got) {
+                    int32_t c = (int32_t)(t - n1);
+                    if (ordered) {
+                        c = t < n0 ? q.acc[t] : t < n1 ? q.att[t - n0] : q.cell[t - n1];
+                        asm volatile("" : "+v"(c));  // (the wait for it: here, not in both branches' wake)
+                        first = t < n1;
+                    }
+                    if (c != -1 || !ordered) {
+                        cell = (uint32_t)c;
                         cfl = 0;
                         if (load(cell, true)) {
                             active = true;
@@ -545,25 +596,18 @@ __global__ __launch_bounds__(CHEM_THREADS, CHEM_WAVES) void k_chem_all(const KCh
             if (exhausted) break;
             continue;
         }
-        if (active && chem_attempt<CM, V>(k, k.rates, rt, cc, s, cfl)) {
+        // every lane attempts (an exec mask around it would copy the state)
+        const bool done = chem_attempt<CM, V>(k, k.rates, rt, cc, s, cfl);
+        if (active && done) {
             finish();
             active = false;
         }
+        if (!active) idle();
     }
     if (io.hist) hist_flush(s_hist, io.hist);
     block_stats(st, a_acc, a_att, a_max, fl);
 }
 
-
-// Positions a wave reserves at a time in the sweep: a quarter of a wave's
-// share of the grid, between one wave's width and CHEM_SWEEP_CHUNK (on a
-// small grid large reservations would leave the work to a few waves).
-static unsigned chem_sweep_chunk(size_t ncell, unsigned waves)
-{
-    const size_t share = ncell / waves / 4;
-    const size_t c = share < TAIL_CHUNK ? TAIL_CHUNK : (share > CHEM_SWEEP_CHUNK ? CHEM_SWEEP_CHUNK : share);
-    return (unsigned)c;
-}
 
 // workgroups of a persistent chemistry kernel: one per CU, and no more than
 // there are wave's widths of cells
@@ -577,6 +621,18 @@ template <typename R, int M, int V>
 static void launch_M(ChemPass pass, const ChemCall<R> &a, hipStream_t s)
 {
     const dim3 hb((unsigned)((a.g.ncell + 255) / 256)), pb(chem_blocks(a.g.ncell));
+    // The one-pass chemistry orders the cells where there are more of them
+    // than lanes (and scratch for it): with at most one cell per lane nothing
+    // is refilled and the order only costs its launch (us per step, ordered /
+    // not: 16^3 91.5 / 82.3, isothermal 32^3 65 / 61, 97 x 61 x 45 222 / 255,
+    // 64^3 304 / 320).
+    const bool more = a.io.ncell > (size_t)CHEM_BLOCKS * CHEM_THREADS;
+    const bool ordered = more && a.io.prev_att && (size_t)a.q.stride >= a.io.ncell;
+    const unsigned slabs = ordered ? CHEM_XCDS : 1u;
+    // without the order: one counter for every wave, so more at a time
+    const unsigned chunk = more && !ordered ? CHEM_SWEEP_CHUNK : 64u;
+    QueueView qa = a.q;
+    qa.slab = ordered ? (unsigned *)a.q.v : a.q.head;
     if (pass != CHEM_TAIL) hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(64), 0, s, a.q.count, 65);
     switch (pass) {
     case CHEM_HEAD:
@@ -595,13 +651,14 @@ static void launch_M(ChemPass pass, const ChemCall<R> &a, hipStream_t s)
         hipLaunchKernelGGL((k_tail<R, M, V>), pb, dim3(CHEM_THREADS), 0, s, a.dk, a.io, a.q, a.st);
         break;
     case CHEM_ALL:
-        // queue counters reset, the lists, then the persistent kernel
-        if (a.io.prev_att && a.io.ncell > 0)
-            hipLaunchKernelGGL(k_order, dim3((unsigned)((a.io.ncell + 4 * ORDER_THREADS - 1) / (4 * ORDER_THREADS))),
+        // queue counters reset, the order (where the scratch has room for
+        // it), then the persistent kernel
+        if (ordered)
+            hipLaunchKernelGGL(k_order, dim3((unsigned)((a.io.ncell + ORDER_CELLS - 1) / ORDER_CELLS)),
                                dim3(ORDER_THREADS), 0, s, a.io.prev_att, a.isothermal ? nullptr : a.io.T, a.io.ncell,
-                               a.q);
-        hipLaunchKernelGGL((k_chem_all<R, M, V>), pb, dim3(CHEM_THREADS), 0, s, a.dk, a.dt, a.io, a.q,
-                           chem_sweep_chunk(a.io.ncell, pb.x * (CHEM_THREADS / 64)), a.st);
+                               qa);
+        hipLaunchKernelGGL((k_chem_all<R, M, V>), pb, dim3(CHEM_THREADS), 0, s, a.dk, a.dt, a.io, qa, ordered, slabs,
+                           ordered ? (unsigned)ORDER_CELLS : chunk, chunk, a.st);
         break;
     }
 }

@@ -333,14 +333,19 @@ struct Rates {
 
     // the coefficients of the fit at offset OX of the global table, OL of the
     // copy; a lane outside the copy reads the global one (a branch no wave of
-    // an ordinary run enters)
+    // an ordinary run enters).  The wait for those loads is kept inside the
+    // branch: behind it every wave would wait there for all its outstanding
+    // memory operations, the stores of the cells just finished among them
     template <int OX, int OL>
     __device__ __forceinline__ RateCoef fit(const RateAt &a) const
     {
         if constexpr (!LDS) return rate_coef<RT_XNI>(x + OX, a.n);
         const uint32_t n = a.n - (uint32_t)RT_LOFF;
         RateCoef c = rate_coef<RT_LNI>(l + OL, n < (uint32_t)RT_LNI ? n : 0u);
-        if (__builtin_expect(n >= (uint32_t)RT_LNI, 0)) c = rate_coef<RT_XNI>(x + OX, a.n);
+        if (__builtin_expect(n >= (uint32_t)RT_LNI, 0)) {
+            c = rate_coef<RT_XNI>(x + OX, a.n);
+            loaded(c);
+        }
         return c;
     }
     template <int OX, int OL>
@@ -356,7 +361,10 @@ struct Rates {
         if constexpr (!LDS) return x[OX + o];
         const uint32_t n = o - (uint32_t)(RT_LOFF / RT_SUB);
         double v = l[OL + (n < (uint32_t)RT_LNOCT ? n : 0u)];
-        if (__builtin_expect(n >= (uint32_t)RT_LNOCT, 0)) v = x[OX + o];
+        if (__builtin_expect(n >= (uint32_t)RT_LNOCT, 0)) {
+            v = x[OX + o];
+            loaded(v);
+        }
         return v;
     }
 

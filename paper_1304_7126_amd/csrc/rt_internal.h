@@ -121,9 +121,11 @@ hipError_t launch_ledger(int mode, const double *acct, unsigned nblk, const doub
 // three regions the tail works off in order: cells that took many attempts
 // in the previous pass, cells that accepted no substep in this one's first
 // attempts, the rest.  A region that is full passes its cells to the next.
+constexpr unsigned QUEUE_SLAB_STRIDE = 64;  // words: two cache lines
 struct QueueView {
     unsigned *count;    // the counter block: [0] region 2, [1] cells taken by the tail, [32] region 1, [64] region 0
     unsigned *head;
+    unsigned *slab;     // one-pass chemistry: positions taken per slab, QUEUE_SLAB_STRIDE apart
     unsigned *cnt[3];   // cells queued per region (each on its own cache line)
     unsigned rbeg[3], rlen[3];  // region offsets and sizes
     int32_t *cell, *acc, *att;
@@ -170,8 +172,8 @@ size_t queue_cell_bytes(bool smooth);
 QueueView queue_view(void *scratch, unsigned cap, unsigned layout_cap);
 
 // the chemistry in one persistent pass over all cells (same results as the
-// head and tail passes); the queue's counters and cell array hold its
-// position counter and its list of long chains
+// head and tail passes); the queue's counters and arrays hold its position
+// counters and the order it takes the cells in
 hipError_t launch_chem_all(bool fp32, const KGrid &g, const KChem &kc, const KChem *dk, double dt, void *N, void *F,
                            double *xHII, double *xHeII, double *xHeIII, double *T, const double *nH, int32_t *nacc,
                            int32_t *natt, const QueueView &q, unsigned long long *hist, const SmoothArgs *sm, double a,

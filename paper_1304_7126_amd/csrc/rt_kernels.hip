@@ -264,6 +264,7 @@ QueueView queue_view(void *scratch, unsigned cap, unsigned layout_cap)
     QueueView q;
     q.count = (unsigned *)b;
     q.head = q.count + 1;
+    q.slab = q.head;
     q.cnt[0] = q.count + 64;
     q.cnt[1] = q.count + 32;
     q.cnt[2] = q.count;

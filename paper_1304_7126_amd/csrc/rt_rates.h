@@ -273,6 +273,12 @@ __host__ __device__ inline void loaded(RateCoef &r)
 #endif
 }
 // (two intervals at once)
+__host__ __device__ inline void loaded(double &v)
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("" : "+v"(v));
+#endif
+}
 __host__ __device__ inline void loaded(RateCoef &a, RateCoef &b)
 {
 #ifdef __HIP_DEVICE_COMPILE__

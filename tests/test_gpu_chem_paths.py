@@ -162,3 +162,23 @@ def test_one_pass_at_the_ends_of_the_lds_rate_table(lo, hi):
     fl, nacc, natt = o.thermochem(st, ctxs[0].courant_dt(), want_counts=True)
     st["nacc"], st["natt"] = nacc, natt
     chem_compare(ctxs[1].state_numpy(), st)
+
+
+@pytest.mark.parametrize("n,fp32,smooth,otsa,cap", [
+    (50, True, False, True, None),    # 125,000 cells: one per lane, in grid order
+    (51, True, False, True, None),    # 132,651: ordered, the last piece of 1,579 cells
+    (51, False, False, True, None),
+    (51, True, True, True, None),
+    (51, False, False, False, None),
+    (64, True, False, True, 0),       # 64 pieces, eight to a slab; a queue the two passes do not have
+])
+def test_one_pass_in_sorted_pieces(n, fp32, smooth, otsa, cap):
+    # a state just set (warm gas listed), then counts of earlier steps and
+    # chains of 48 attempts and more on the lists
+    w, (a, b) = lognormal_pair(n, fp32, 0.1, smooth=smooth, otsa=otsa, steps=4, queue_cap=cap)
+    dt = a.courant_dt()
+    for _ in range(w.steps):
+        a.step(dt, 1)
+        b.step(dt, 1)
+    s = compare(a, b)
+    assert s["attempts_max"] >= 48
