@@ -2,13 +2,13 @@
 // uneven size (and 1-3 photon groups each) advanced together, one graph
 // launch per step.
 //
-// A step is: k_binject (all boxes' sources), k_bhead (persistent: waves pop
-// 64-cell chunks of any box from one queue ordered largest box first, then
-// transport and the first K chemistry attempts of each chunk; a chunk never
-// straddles two boxes, so box constants stay uniform across the wave),
-// k_btail (persistent: lanes refill themselves with the cells still
-// subcycling, whatever their box).  No wave ever waits on another, so every
-// wave exits once the queues are drained.
+// A step is: k_binject (all boxes' sources), k_btransport (a wave per 64-cell
+// chunk and group), k_bhead (persistent workgroups: the first K chemistry
+// attempts of four chunks at a time, in the order of the chunks, largest box
+// first; a chunk never straddles two boxes, so box constants stay uniform
+// across the wave), k_btail (persistent: lanes refill themselves with the
+// cells still subcycling, whatever their box).  No wave waits on another
+// workgroup, so every wave exits once the work is handed out.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -31,7 +31,6 @@ struct BoxDev {
     double *xHII, *xHeII, *xHeIII, *T;
     const double *nH;
     int32_t *nacc, *natt;
-    const KChem *kchem;
 };
 
 struct Chunk {
@@ -44,31 +43,40 @@ struct BSrc {
     double rate[3];
 };
 
-// scratch: [3 counters + pad: 256 B][cell, box, acc, att: 4 x cap int32][QV x cap doubles]
+// scratch: [4 counters: 512 B][cell, box, acc, att: 4 x cap int32][QV x cap doubles]
 struct BQueue {
-    unsigned *ctr;  // [0] chunks taken, [1] cells queued, [2] queued cells taken
+    // queued cells taken, and cells offered to the regions (a cache line each)
+    unsigned *ctr;
     int32_t *cell, *box, *acc, *att;
     double *v;
-    unsigned cap;
+    // regions of long chains, warm and cold gas
+    unsigned rbeg[3], rlen[3];
 };
+
+constexpr int BQ_LINE = 32, BQ_TAKEN = 3 * BQ_LINE;  // words of ctr: region r at r * BQ_LINE
 
 static size_t al256(size_t b) { return (b + 255) & ~(size_t)255; }
 
-static size_t bqueue_bytes(unsigned cap) { return 256 + al256((size_t)cap * 4 * 4) + (size_t)QV * cap * 8; }
+static size_t bqueue_bytes(unsigned cap) { return 512 + al256((size_t)cap * 4 * 4) + (size_t)QV * cap * 8; }
 
 static BQueue bqueue_view(void *scratch, unsigned cap, unsigned layout_cap)
 {
     char *b = (char *)scratch;
     BQueue q;
     q.ctr = (unsigned *)b;
-    b += 256;
+    b += 512;
     q.cell = (int32_t *)b;
     q.box = q.cell + layout_cap;
     q.acc = q.box + layout_cap;
     q.att = q.acc + layout_cap;
     b += al256((size_t)layout_cap * 16);
     q.v = (double *)b;
-    q.cap = cap;
+    q.rbeg[0] = 0;
+    q.rlen[0] = cap / 8;
+    q.rbeg[1] = q.rlen[0];
+    q.rlen[1] = (cap - q.rlen[0]) / 2;
+    q.rbeg[2] = q.rbeg[1] + q.rlen[1];
+    q.rlen[2] = cap - q.rbeg[2];
     return q;
 }
 
@@ -157,17 +165,52 @@ __global__ void k_binject_t(const BoxDev *__restrict__ boxes, const BSrc *__rest
     }
 }
 
-__global__ void k_bzero(unsigned *p) { if (threadIdx.x < 3) p[threadIdx.x] = 0u; }
+__global__ void k_bzero(unsigned *p) { p[threadIdx.x] = 0u; }  // 128 words
 
-// one 64-cell chunk of box b: transport of the M groups from the source
-// set, then up to K chemistry attempts; the unfinished cells are queued
-template <typename R, int M, int FLUX>
-__device__ __forceinline__ void head_chunk(const BoxDev &b, uint32_t box, uint32_t start, int src, double dt, R c,
-                                           const R *__restrict__ tab, int nf, int nth, const BQueue &q,
-                                           unsigned stride, int K, const double *rx, const double *rt, unsigned long long &a_acc,
-                                           unsigned long long &a_att, unsigned long long &a_max, unsigned &fl)
+// Transport of every box's groups, source set -> destination set: a wave per
+// 64-cell chunk and group (blockIdx.y).  A kernel of its own: its loads of the
+// neighbours need many waves to hide their latency, which the chemistry's
+// registers and its table in LDS leave no room for (transport in the head
+// pass: 930 us per launch for ten boxes of the batch benchmark, 73% of it
+// waiting, against 65 here and 290 for the head without it).  Each XCD (workgroup b is on XCD b % 8) takes a
+// contiguous range of the chunks, so that the halos meet in its L2.
+template <typename R, int FLUX>
+__global__ __launch_bounds__(256) void k_btransport(const BoxDev *__restrict__ boxes, const Chunk *__restrict__ chunks,
+                                                    unsigned nchunks, int src, R c, const R *__restrict__ tab, int nf,
+                                                    int nth)
 {
-    const KChem &k = *b.kchem;
+    const unsigned per = gridDim.x / 8u;  // the grid is a multiple of 8
+    const unsigned blk = (blockIdx.x % 8u) * per + blockIdx.x / 8u;
+    const unsigned ci = __builtin_amdgcn_readfirstlane(blk * 4u + (threadIdx.x >> 6));
+    if (ci >= nchunks) return;
+    const Chunk ch = chunks[ci];
+    const BoxDev &b = boxes[ch.box];
+    const int grp = (int)blockIdx.y;
+    const uint32_t i = ch.start + (threadIdx.x & 63u);
+    if (grp >= b.M || i >= (uint32_t)b.g.ncell) return;
+    const size_t nc = b.g.ncell;
+    int ix, iy, iz;
+    cell_coords(b.g, i, ix, iy, iz);
+    const Nbr nb = neighbours(b.g, i, ix, iy, iz);
+    double bout = 0.0;  // boundary outflow (not accounted in batches)
+    const U4<R> o = transport_cell<R, FLUX>(nb, i, nc, (const R *)b.N[src] + (size_t)grp * nc,
+                                            (const R *)b.F[src] + (size_t)3 * grp * nc, c, (R)b.kdx, tab, nf, nth, bout,
+                                            b.g, grp);
+    R *F = (R *)b.F[1 - src] + (size_t)3 * grp * nc + i;
+    ((R *)b.N[1 - src])[(size_t)grp * nc + i] = o.n;
+    F[0] = o.fx;
+    F[nc] = o.fy;
+    F[2 * nc] = o.fz;
+}
+
+// one 64-cell chunk of box b: up to K chemistry attempts on the transported
+// state in the destination set; the unfinished cells are queued
+template <typename R>
+__device__ __forceinline__ void head_chunk(const BoxDev &b, const KChem &k, uint32_t box, uint32_t start, int dst,
+                                           double dt, const BQueue &q, unsigned stride, int K, const double *rx,
+                                           const double *rt, unsigned long long &a_acc, unsigned long long &a_att,
+                                           unsigned long long &a_max, unsigned &fl)
+{
     const int lane = (int)(threadIdx.x & 63u);
     const uint32_t i = start + (uint32_t)lane;
     const bool valid = i < (uint32_t)b.g.ncell;
@@ -175,32 +218,24 @@ __device__ __forceinline__ void head_chunk(const BoxDev &b, uint32_t box, uint32
     CS s;
     CC cc{1.0, 0.0, 0.0, 0.0};
     bool done = true;
-    // the transported flux stays in registers: a queued cell's goes to the
-    // destination for the tail, a finished cell's is written once, rescaled
-    R fo[3 * M];
+    R fo[9] = {};
 #pragma unroll
     for (int g = 0; g < 3; ++g) {
         s.N[g] = 0.0;
         s.fs[g] = 1.0;
     }
     if (valid) {
-        int ix, iy, iz;
-        cell_coords(b.g, i, ix, iy, iz);
-        const Nbr nb = neighbours(b.g, i, ix, iy, iz);
-        const R *Nin = (const R *)b.N[src];
-        const R *Fin = (const R *)b.F[src];
+        const R *N = (const R *)b.N[dst] + i, *F = (const R *)b.F[dst] + i;
         bool fin = true;
 #pragma unroll
-        for (int grp = 0; grp < M; ++grp) {
-            double bout = 0.0;  // boundary outflow (not accounted in batches)
-            const U4<R> o = transport_cell<R, FLUX>(nb, i, nc, Nin + (size_t)grp * nc, Fin + (size_t)3 * grp * nc, c,
-                                                    (R)b.kdx, tab, nf, nth, bout, b.g, grp);
-            s.N[grp] = (double)o.n;
-            fo[3 * grp] = o.fx;
-            fo[3 * grp + 1] = o.fy;
-            fo[3 * grp + 2] = o.fz;
-            fin = fin && isfinite(o.fx) && isfinite(o.fy) && isfinite(o.fz);
+        for (int g = 0; g < 3; ++g) {
+            if (g >= b.M) break;
+            s.N[g] = (double)N[(size_t)g * nc];
+#pragma unroll
+            for (int j = 3 * g; j < 3 * g + 3; ++j) fo[j] = F[(size_t)j * nc];
         }
+#pragma unroll
+        for (int j = 0; j < 9; ++j) fin = fin && (j >= 3 * b.M || isfinite(fo[j]));
         s.x = b.xHII[i];
         s.y2 = b.xHeII[i];
         s.y3 = b.xHeIII[i];
@@ -212,105 +247,86 @@ __device__ __forceinline__ void head_chunk(const BoxDev &b, uint32_t box, uint32
             fl |= 2u;
         }
     }
+    // Queue: long chains (by the substep they have come down to), warm gas and
+    // cold gas apart, each to the next region when its own is full.  Long
+    // chains go first in the tail, as one that starts late is all that still
+    // runs at its end; the waves of cold gas skip the Boltzmann factors (more
+    // than half of an attempt's instructions, for the whole wave when one lane
+    // is warm).  One atomic per region and workgroup: with one per wave and
+    // one per chunk, all on one cache line, the atomics alone took the head
+    // pass 900 us for 39,000 chunks (now 290).
+    __shared__ unsigned s_n[3], s_base[3];
     const bool want = !done;
-    const unsigned long long m = __ballot(want);
-    bool queued = false;
-    if (m) {
-        const int leader = __ffsll((long long)m) - 1;
-        unsigned base = 0;
-        if (lane == leader) base = atomicAdd(q.ctr + 1, (unsigned)__popcll(m));
-        base = __shfl(base, leader);
-        if (want) {
-            const unsigned p = base + (unsigned)__popcll(m & ((1ull << lane) - 1ull));
-            if (p < q.cap) {
-                bq_store(q, stride, p, box, i, s);
-                R *Fout = (R *)b.F[1 - src];
-#pragma unroll
-                for (int j = 0; j < 3 * M; ++j) Fout[(size_t)j * nc + i] = fo[j];
-                queued = true;
-            }
+    const int cls = s.rem > 16.0 * s.h ? 0 : s.Tmu * mu_of(k, s.x, s.y2, s.y3) > T_COLD_COOL ? 1 : 2;
+    unsigned p = ~0u;
+    for (int a = 0; a < 3; ++a) {
+        const bool cand = want && p == ~0u;
+        const int region = (cls + a) % 3;
+        unsigned j = 0;
+        if (threadIdx.x < 3) s_n[threadIdx.x] = 0u;
+        __syncthreads();
+        if (cand) j = atomicAdd(&s_n[region], 1u);
+        __syncthreads();
+        if (threadIdx.x < 3 && s_n[threadIdx.x])
+            s_base[threadIdx.x] = atomicAdd(q.ctr + threadIdx.x * BQ_LINE, s_n[threadIdx.x]);
+        __syncthreads();
+        if (cand) {
+            j += s_base[region];
+            if (j < q.rlen[region]) p = q.rbeg[region] + j;
         }
+        if (!__syncthreads_or(want && p == ~0u)) break;
     }
+    const bool queued = p != ~0u;
+    if (queued) bq_store(q, stride, p, box, i, s);
     if (want && !queued) {
         while (!done) done = chem_attempt<CM>(k, rx, rt, cc, s, fl);
     }
     if (valid && !queued) {
         const double T = chem_finish<CM>(k, cc, s, fl);
-        bstore<R>(b, 1 - src, i, s, T, fo);
+        bstore<R>(b, dst, i, s, T, fo);
         a_acc += (unsigned long long)s.acc;
         a_att += (unsigned long long)s.att;
         a_max = a_max > (unsigned long long)s.att ? a_max : (unsigned long long)s.att;
     }
 }
 
-__device__ __forceinline__ void bblock_stats(DevStats *st, unsigned long long acc, unsigned long long att,
-                                             unsigned long long mx, unsigned fl)
-{
-    __shared__ unsigned long long s_acc[256], s_att[256], s_max[256];
-    __shared__ unsigned s_fl[256];
-    const int t = threadIdx.x;
-    s_acc[t] = acc;
-    s_att[t] = att;
-    s_max[t] = mx;
-    s_fl[t] = fl;
-    __syncthreads();
-    for (int o = 128; o > 0; o >>= 1) {
-        if (t < o) {
-            s_acc[t] += s_acc[t + o];
-            s_att[t] += s_att[t + o];
-            s_max[t] = s_max[t] > s_max[t + o] ? s_max[t] : s_max[t + o];
-            s_fl[t] |= s_fl[t + o];
-        }
-        __syncthreads();
-    }
-    if (t == 0) {
-        if (s_att[0]) {
-            atomicAdd(&st->acc_total, s_acc[0]);
-            atomicAdd(&st->att_total, s_att[0]);
-            atomicMax(&st->att_max, s_max[0]);
-        }
-        if (s_fl[0]) atomicOr(&st->flags, s_fl[0]);
-    }
-}
-
-template <typename R, int FLUX>
-__global__ __launch_bounds__(256) void k_bhead(const BoxDev *__restrict__ boxes, const double *__restrict__ rx, const Chunk *__restrict__ chunks,
-                                               unsigned nchunks, BQueue q, unsigned stride, int K, int src,
-                                               double dt, R c, const R *__restrict__ tab, int nf, int nth,
+template <typename R>
+__global__ __launch_bounds__(256) void k_bhead(const BoxDev *__restrict__ boxes, const KChem *__restrict__ kc,
+                                               const double *__restrict__ rx, const Chunk *__restrict__ chunks,
+                                               unsigned nchunks, BQueue q, unsigned stride, int K, int dst, double dt,
                                                DevStats *__restrict__ st)
 {
-    const int lane = (int)(threadIdx.x & 63u);
     __shared__ double rt[rate_table_len<0>()];
     rate_table_to_lds<0>(rx, rt);
     unsigned long long a_acc = 0, a_att = 0, a_max = 0;
     unsigned fl = 0;
-    while (true) {
-        unsigned ci = 0;
-        if (lane == 0) ci = atomicAdd(q.ctr, 1u);
-        ci = __shfl(ci, 0);
-        if (ci >= nchunks) break;
-        const Chunk ch = chunks[ci];
+    // the waves of a workgroup take a quad of chunks together (they queue
+    // together); a wave past the last chunk has no cells
+    for (unsigned c0 = 4u * blockIdx.x; c0 < nchunks; c0 += 4u * gridDim.x) {
+        const unsigned ci = __builtin_amdgcn_readfirstlane(c0 + (threadIdx.x >> 6));
+        Chunk ch = chunks[ci < nchunks ? ci : nchunks - 1u];
         const BoxDev &b = boxes[ch.box];
-        if (b.M == 1)
-            head_chunk<R, 1, FLUX>(b, ch.box, ch.start, src, dt, c, tab, nf, nth, q, stride, K, rx, rt, a_acc, a_att, a_max, fl);
-        else if (b.M == 2)
-            head_chunk<R, 2, FLUX>(b, ch.box, ch.start, src, dt, c, tab, nf, nth, q, stride, K, rx, rt, a_acc, a_att, a_max, fl);
-        else
-            head_chunk<R, 3, FLUX>(b, ch.box, ch.start, src, dt, c, tab, nf, nth, q, stride, K, rx, rt, a_acc, a_att, a_max, fl);
+        if (ci >= nchunks) ch.start = (uint32_t)b.g.ncell;
+        head_chunk<R>(b, kc[ch.box], ch.box, ch.start, dst, dt, q, stride, K, rx, rt, a_acc, a_att, a_max, fl);
     }
-    bblock_stats(st, a_acc, a_att, a_max, fl);
+    block_stats(st, a_acc, a_att, a_max, fl);
 }
 
 // Tail: lanes hold cells of any box (the attempt runs with three groups, as
-// in every chemistry kernel).
+// in every chemistry kernel).  What bounds it is the longest chain (135
+// attempts of the benchmark's ten boxes, about 4 us each): 790 us per launch
+// with the long chains anywhere in the queue, 615 with them first.  Two
+// workgroups fit a CU (the rate table in LDS), so 512 of them.
 template <typename R>
-__global__ __launch_bounds__(256) void k_btail(const BoxDev *__restrict__ boxes, const double *__restrict__ rx, BQueue q, unsigned stride, int dst,
+__global__ __launch_bounds__(256) void k_btail(const BoxDev *__restrict__ boxes, const KChem *__restrict__ kc, const double *__restrict__ rx, BQueue q, unsigned stride, int dst,
                                                double dt, DevStats *__restrict__ st)
 {
     const int lane = (int)(threadIdx.x & 63u);
     __shared__ double rt[rate_table_len<0>()];
     rate_table_to_lds<0>(rx, rt);
-    const unsigned n = min(q.ctr[1], q.cap);
+    // the regions in order
+    const unsigned n0 = min(q.ctr[0], q.rlen[0]), n1 = n0 + min(q.ctr[BQ_LINE], q.rlen[1]);
+    const unsigned n = n1 + min(q.ctr[2 * BQ_LINE], q.rlen[2]);
     CS s;
     R fpre[9];  // the cell's transported flux, loaded with the cell (used when it is written)
     uint32_t cell = 0, box = 0;
@@ -337,7 +353,7 @@ __global__ __launch_bounds__(256) void k_btail(const BoxDev *__restrict__ boxes,
                     const unsigned take = more > TAIL_CHUNK ? more : TAIL_CHUNK;
                     const int leader = __ffsll((long long)m) - 1;
                     unsigned base = 0;
-                    if (lane == leader) base = atomicAdd(q.ctr + 2, take);
+                    if (lane == leader) base = atomicAdd(q.ctr + BQ_TAKEN, take);
                     base = __shfl(base, leader);
                     p = r < ravail ? rbase + r : base + (r - ravail);
                     rbase = base + more;
@@ -345,9 +361,9 @@ __global__ __launch_bounds__(256) void k_btail(const BoxDev *__restrict__ boxes,
                 }
                 if (rbase >= n) exhausted = true;
                 if (need && p < n) {
-                    bq_load(q, stride, p, box, cell, s);
+                    bq_load(q, stride, p < n0 ? p : p < n1 ? q.rbeg[1] + (p - n0) : q.rbeg[2] + (p - n1), box, cell, s);
                     const BoxDev &bb = boxes[box];
-                    cc = make_cc(*bb.kchem, bb.nH[cell], bb.T[cell]);
+                    cc = make_cc(kc[box], bb.nH[cell], bb.T[cell]);
                     const R *F = (const R *)bb.F[dst];
 #pragma unroll
                     for (int j = 0; j < 9; ++j) fpre[j] = j < 3 * bb.M ? F[(size_t)j * bb.g.ncell + cell] : R(0);
@@ -356,8 +372,7 @@ __global__ __launch_bounds__(256) void k_btail(const BoxDev *__restrict__ boxes,
             }
         }
         if (!__any(active)) break;
-        if (active) {
-            const KChem &k = *boxes[box].kchem;
+        auto step = [&](const KChem &k) {
             if (chem_attempt<CM>(k, rx, rt, cc, s, fl)) {
                 const double T = chem_finish<CM>(k, cc, s, fl);
                 bstore<R>(boxes[box], dst, cell, s, T, fpre);
@@ -366,9 +381,17 @@ __global__ __launch_bounds__(256) void k_btail(const BoxDev *__restrict__ boxes,
                 a_max = a_max > (unsigned long long)s.att ? a_max : (unsigned long long)s.att;
                 active = false;
             }
+        };
+        // a wave whose lanes are all in one box (most: cells are queued chunk
+        // by chunk) reads the box's constants as scalars
+        const uint32_t b0 = __builtin_amdgcn_readlane(box, __ffsll((long long)__ballot(active)) - 1);
+        if (!__any(active && box != b0)) {
+            if (active) step(kc[b0]);
+        } else {
+            if (active) step(kc[box]);
         }
     }
-    bblock_stats(st, a_acc, a_att, a_max, fl);
+    block_stats(st, a_acc, a_att, a_max, fl);
 }
 
 }  // namespace rtm1
@@ -405,9 +428,9 @@ struct rt_batch {
     int cur = 0;
     hipStream_t stream = nullptr;
     // tuning
-    int head_blocks_per_cu = 4;
+    int head_blocks_per_cu = 2;  // what the rate table in LDS leaves room for
     int head_attempts = HEAD_ATTEMPTS;
-    int tail_blocks = TAIL_BLOCKS;
+    int tail_blocks = 512;
     int use_graph = 1;
     int ncu = 256;
     // graphs of one step starting from set 0 and from set 1
@@ -572,7 +595,6 @@ extern "C" rt_status rt_batch_init(int nbox, const rt_grid *grids, const rt_grou
         rt_batch_free(b);
         return RT_ENOMEM;
     }
-    for (int i = 0; i < nbox; ++i) b->boxes[i].kchem = b->dkchem + i;
     *out = b;
     return RT_OK;
 }
@@ -700,7 +722,7 @@ static rt_status enqueue_step(rt_batch *b, double dt, int src)
 {
     const BQueue q = bqueue_view(b->scratch, b->qcap, b->qcap_max);
     hipStream_t s = b->stream;
-    hipLaunchKernelGGL(k_bzero, dim3(1), dim3(64), 0, s, q.ctr);
+    hipLaunchKernelGGL(k_bzero, dim3(1), dim3(128), 0, s, q.ctr);
     if (b->nsrc > 0) {
         if (b->fp32)
             hipLaunchKernelGGL(k_binject_t<float>, dim3((b->nsrc + 63) / 64), dim3(64), 0, s, b->dboxes, b->dsrc, b->nsrc,
@@ -711,18 +733,23 @@ static rt_status enqueue_step(rt_batch *b, double dt, int src)
     }
     const unsigned hb = (unsigned)(b->head_blocks_per_cu * b->ncu);
     const unsigned tb = (unsigned)b->tail_blocks;
+    const dim3 xb(((b->nchunks + 3) / 4 + 7) / 8 * 8, 3);
     if (b->fp32) {
-        auto hk = b->flux ? k_bhead<float, 1> : k_bhead<float, 0>;
-        hipLaunchKernelGGL(hk, dim3(hb), dim3(256), 0, s, b->dboxes, b->drates, b->dchunks, b->nchunks, q, b->qcap_max,
-                           b->head_attempts, src, dt, (float)b->c_r, (const float *)b->hll, b->nf, b->nth, b->dstats);
-        hipLaunchKernelGGL(k_btail<float>, dim3(tb), dim3(256), 0, s, b->dboxes, b->drates, q, b->qcap_max, 1 - src, dt,
-                           b->dstats);
+        auto xk = b->flux ? k_btransport<float, 1> : k_btransport<float, 0>;
+        hipLaunchKernelGGL(xk, xb, dim3(256), 0, s, b->dboxes, b->dchunks, b->nchunks, src, (float)b->c_r,
+                           (const float *)b->hll, b->nf, b->nth);
+        hipLaunchKernelGGL(k_bhead<float>, dim3(hb), dim3(256), 0, s, b->dboxes, b->dkchem, b->drates, b->dchunks,
+                           b->nchunks, q, b->qcap_max, b->head_attempts, 1 - src, dt, b->dstats);
+        hipLaunchKernelGGL(k_btail<float>, dim3(tb), dim3(256), 0, s, b->dboxes, b->dkchem, b->drates, q, b->qcap_max,
+                           1 - src, dt, b->dstats);
     } else {
-        auto hk = b->flux ? k_bhead<double, 1> : k_bhead<double, 0>;
-        hipLaunchKernelGGL(hk, dim3(hb), dim3(256), 0, s, b->dboxes, b->drates, b->dchunks, b->nchunks, q, b->qcap_max,
-                           b->head_attempts, src, dt, b->c_r, (const double *)b->hll, b->nf, b->nth, b->dstats);
-        hipLaunchKernelGGL(k_btail<double>, dim3(tb), dim3(256), 0, s, b->dboxes, b->drates, q, b->qcap_max, 1 - src, dt,
-                           b->dstats);
+        auto xk = b->flux ? k_btransport<double, 1> : k_btransport<double, 0>;
+        hipLaunchKernelGGL(xk, xb, dim3(256), 0, s, b->dboxes, b->dchunks, b->nchunks, src, b->c_r,
+                           (const double *)b->hll, b->nf, b->nth);
+        hipLaunchKernelGGL(k_bhead<double>, dim3(hb), dim3(256), 0, s, b->dboxes, b->dkchem, b->drates, b->dchunks,
+                           b->nchunks, q, b->qcap_max, b->head_attempts, 1 - src, dt, b->dstats);
+        hipLaunchKernelGGL(k_btail<double>, dim3(tb), dim3(256), 0, s, b->dboxes, b->dkchem, b->drates, q, b->qcap_max,
+                           1 - src, dt, b->dstats);
     }
     BT_HIP(b, hipGetLastError());
     return RT_OK;

@@ -565,6 +565,45 @@ __device__ __forceinline__ double chem_finish(const KChem &k, const CC &cc, cons
     return T;
 }
 
+// Reduction of the chemistry counters: butterflies in each wave, then the
+// block's waves in LDS; one set of atomics per block.
+__device__ __forceinline__ void block_stats(DevStats *st, unsigned long long acc, unsigned long long att,
+                                            unsigned long long mx, unsigned fl)
+{
+    __shared__ unsigned long long s_st[16][3];
+    __shared__ unsigned s_fl[16];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        acc += __shfl_xor(acc, o, 64);
+        att += __shfl_xor(att, o, 64);
+        const unsigned long long m = __shfl_xor(mx, o, 64);
+        mx = m > mx ? m : mx;
+        fl |= __shfl_xor(fl, o, 64);
+    }
+    const unsigned w = threadIdx.x >> 6;
+    if ((threadIdx.x & 63u) == 0) {
+        s_st[w][0] = acc;
+        s_st[w][1] = att;
+        s_st[w][2] = mx;
+        s_fl[w] = fl;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        for (unsigned j = 1; j < (blockDim.x + 63u) >> 6; ++j) {
+            acc += s_st[j][0];
+            att += s_st[j][1];
+            mx = s_st[j][2] > mx ? s_st[j][2] : mx;
+            fl |= s_fl[j];
+        }
+        if (att) {
+            atomicAdd(&st->acc_total, acc);
+            atomicAdd(&st->att_total, att);
+            atomicMax(&st->att_max, mx);
+        }
+        if (fl) atomicOr(&st->flags, fl);
+    }
+}
+
 // Queue of cells still subcycling after the head pass (structure of arrays
 // in caller scratch): the cell index, the attempt counters, and the partial
 // state {N[3], fs[3], x_HII, x_HeII, x_HeIII, T_mu, rem, h}; the grid's queue

@@ -182,3 +182,21 @@ def test_batching_workload_subset_mixed_matches_oracle():
         # FP32 rounding of N, F once per step, carried through the chemistry
         for k in ("xHII", "xHeII", "xHeIII", "T", "N", "F"):
             assert rel_err(g[k], st[k]) < 1e-5, (side, k, rel_err(g[k], st[k]))
+
+
+@pytest.mark.parametrize("sides,fp32", [((1,), True), ((3, 1), False), ((7, 9, 5), True), ((20, 20, 20), False)])
+def test_batch_regions_of_the_queue(sides, fp32):
+    # chunks that do not fill a quad, boxes of a few cells, and one attempt
+    # in the head pass: most cells are of one class, more than its region of
+    # the queue holds
+    specs = [ri.BoxSpec(side=s, M=1 + i % 3, nH=1e-2, n_sources=1 + (s > 9) * 40, seed=70 + i)
+             for i, s in enumerate(sides)]
+    b, ws, srcs = make_batch(specs, fp32, head_attempts=1, tail_blocks=3)
+    dt = b.courant_dt()
+    b.step(dt, 6)
+    for i, w in enumerate(ws):
+        ctx = single(w, srcs[i], fp32)
+        ctx.step(dt, 6)
+        g1, g2 = b.state_numpy(i), ctx.state_numpy()
+        for k in FIELDS:
+            assert np.array_equal(g1[k], g2[k]), (i, k)
