@@ -372,7 +372,7 @@ typedef struct rt_batch rt_batch;
 rt_status rt_batch_init(int nbox, const rt_grid *grids, const rt_groups *groups, const rt_params *params,
                         rt_batch **out);
 
-/* Device scratch the batch needs (chunk counter and the queue of cells still
+/* Device scratch the batch needs (counters and the queue of cells still
  * subcycling, with room for every cell). */
 size_t rt_batch_scratch_bytes(const rt_batch *b);
 

@@ -827,11 +827,11 @@ static SmoothArgs smooth_args(const rt_ctx *c, int pre_set, bool injected)
 }
 
 // One pass or two for the chemistry after a separate transport: one pass at
-// every size.  Measured with the rate table (us per step, one pass / two
-// passes): 16^3 89 / 103, isothermal 32^3 66 / 94, 97 x 61 x 45 275 / 307,
-// 64^3 354 / 400 (before it the two passes were ahead below 2,000,000
-// cells: the persistent lanes' longer chains of instructions hid less of
-// their latency there).
+// every size.  Measured (us per step, one pass / two passes): 16^3 82 / 103,
+// isothermal 32^3 57 / 94, 97 x 61 x 45 222 / 307, 64^3 304 / 400 (before the
+// rates came from a table the two passes were ahead below 2,000,000 cells: the
+// persistent lanes' longer chains of instructions hid less of their latency
+// there).
 static bool use_one_pass(const rt_ctx *c) { return c->chem_path != RT_CHEM_TWO_PASS; }
 
 static rt_status do_chem(rt_ctx *c, double dt)

@@ -167,9 +167,7 @@ __global__ __launch_bounds__(256, (head_waves<R, M>())) void k_head(KGrid g, con
 // check repeats at once with the halved substep), and refill from the
 // wave's reservation of queue positions as soon as their cell has filled
 // dt_RT, so that a few slow cells do not hold whole waves of finished
-// lanes.  Compiled for three waves per SIMD: the smoothed
-// variants would otherwise take 176-178 VGPRs and run two (a few bytes of
-// spill at three: 4.6 -> 4.0 ms per tail at 256^3 x 3).
+// lanes.
 template <typename R, int M, int V>
 __global__ __launch_bounds__(CHEM_THREADS, CHEM_WAVES) void k_tail(const KChem *__restrict__ kp, ChemIO<R> io, QueueView q, DevStats *__restrict__ st)
 {
@@ -568,7 +566,6 @@ __global__ __launch_bounds__(CHEM_THREADS, CHEM_WAVES) void k_chem_all(const KCh
     if (io.hist) hist_flush(s_hist, io.hist);
     block_stats(st, a_acc, a_att, a_max, fl);
 }
-
 
 // workgroups of a persistent chemistry kernel: one per CU, and no more than
 // there are wave's widths of cells

@@ -160,7 +160,6 @@ struct ChemIO {
     uint8_t *prev_att = nullptr;
 };
 
-constexpr int TAIL_BLOCKS = 1024;
 constexpr int HEAD_ATTEMPTS = 3;
 
 // bytes of scratch for a queue of cap cells (after the reduction partials),

@@ -47,7 +47,8 @@
 namespace rtm1 {
 
 // the fits; a table holds RF_AHII, RF_EHII and the powers of the case in use
-enum { RF_AHII = 0, RF_AHEII = 1, RF_AHEIII = 2, RF_EHII = 3, RF_EHEIII = 4, RF_T397 = 5 };
+// (those of HeIII are hydrogen's at RT_HEIII_SCALE times the temperature)
+enum { RF_AHII, RF_AHEII, RF_EHII, RF_T397 };
 
 // A T^k lam^p (1 + (lam/l0)^q)^-r with lam = TL/T (r = 0: a power of T)
 struct RateFit {
@@ -65,15 +66,9 @@ __host__ __device__ inline RateFit rate_fit(int fit, bool case_a)
     case RF_AHEII:  // alpha_HeII without the dielectronic part
         return case_a ? RateFit{3e-14, 0, 570670.0, 0.654, 1.0, 1.0, 0.0}
                       : RateFit{1.26e-14, 0, 570670.0, 0.75, 1.0, 1.0, 0.0};
-    case RF_AHEIII:  // alpha_HeIII
-        return case_a ? RateFit{2.538e-13, 0, 1263030.0, 1.503, 0.522, 0.47, 1.923}
-                      : RateFit{5.506e-14, 0, 1263030.0, 1.5, 2.74, 0.407, 2.242};
     case RF_EHII:  // recombination cooling of HII
         return case_a ? RateFit{1.778e-29, 1, 315614.0, 1.965, 0.541, 0.502, 2.697}
                       : RateFit{3.435e-30, 1, 315614.0, 1.97, 2.25, 0.376, 3.72};
-    case RF_EHEIII:  // recombination cooling of HeIII
-        return case_a ? RateFit{8.0 * 1.778e-29, 1, 1263030.0, 1.965, 0.541, 0.502, 2.697}
-                      : RateFit{8.0 * 3.435e-30, 1, 1263030.0, 1.97, 2.25, 0.376, 3.72};
     default:  // RF_T397: T^-0.397 of the HeII excitation cooling
         return RateFit{1.0, 0, 1.0, 0.397, 1.0, 1.0, 0.0};
     }
