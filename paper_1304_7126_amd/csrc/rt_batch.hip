@@ -252,7 +252,10 @@ __device__ __forceinline__ void head_chunk(const BoxDev &b, const KChem &k, uint
     // chains go first in the tail, as one that starts late is all that still
     // runs at its end; the waves of cold gas skip the Boltzmann factors (more
     // than half of an attempt's instructions, for the whole wave when one lane
-    // is warm).  One atomic per region and workgroup: with one per wave and
+    // is warm).  Long: 16 or more substeps of the present length left (ten
+    // boxes: 1.04 ms per step; from 8 on 1.10, from 32 on 1.13, so many that
+    // the longest wait, so few that some start late).
+    // One atomic per region and workgroup: with one per wave and
     // one per chunk, all on one cache line, the atomics alone took the head
     // pass 900 us for 39,000 chunks (now 290).
     __shared__ unsigned s_n[3], s_base[3];

@@ -614,10 +614,14 @@ constexpr int QV = 12;
 constexpr int QV_CC = QV;
 constexpr int QV_GRID = QV + 2;
 
-// a queued cell that took at least this many attempts in the previous pass
-// goes to the tail's first region
+// A cell that took at least this many attempts in the previous pass is a long
+// chain, taken first (lists of k_order, first region of the queue).  Measured
+// (us per step at 16 / 20 / 28 / 48 / 80): 256^3 x 3 3,693 / 3,698 / 3,713 /
+// 3,770 / 3,880, 97 x 61 x 45 208 / 207 / 231 / 221 / 233, 128^3 FP64 991 /
+// 995 / 959 / 992 / 1,004, 64^3 302 / 303 / 302 / 305 / 320, shadowed 128^3
+// 753 / 754 / 755 / 753 / 926.
 #ifndef RT_TAIL_LONG_ATTEMPTS
-#define RT_TAIL_LONG_ATTEMPTS 48
+#define RT_TAIL_LONG_ATTEMPTS 20
 #endif
 constexpr int TAIL_LONG_ATTEMPTS = RT_TAIL_LONG_ATTEMPTS;
 constexpr int QV_SMOOTH = QV_GRID + 6;
