@@ -312,7 +312,9 @@ __device__ __forceinline__ bool chem_init(const KChem &k, double dt, double T, b
     s.rem = ok ? dt : 0.0;
     s.h = dt;
     s.acc = 0;
-    s.att = 0;
+    // held at a temperature at which no rate is defined, every attempt would
+    // fail: the cell starts at the cap
+    s.att = ok && k.isothermal && T <= 0.0 ? k.max_att32 : 0;
     return ok;
 }
 

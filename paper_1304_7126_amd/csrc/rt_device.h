@@ -287,7 +287,7 @@ struct vd {
 // h = r/2 approach sqrt(T) and 1/(2 sqrt(T)); one Goldschmidt step on both,
 // then a Newton correction of g from its residual T - g^2 and one more step
 // on h, leave each within an ulp, and 1/T = (2h)^2.  (Zero or negative T
-// gives NaN, and an attempt that fails.)
+// gives NaN, and an attempt that fails: its cooling is NaN.)
 __device__ __forceinline__ void sqrt_and_inv(double T, double &sq, double &inv)
 {
     const double r = __builtin_amdgcn_rsq(T);

@@ -182,3 +182,52 @@ def test_one_pass_in_sorted_pieces(n, fp32, smooth, otsa, cap):
         b.step(dt, 1)
     s = compare(a, b)
     assert s["attempts_max"] >= 48
+
+
+@pytest.mark.parametrize("smooth,otsa", [(False, True), (False, False), (True, True)])
+@pytest.mark.parametrize("path", ["one-pass", "two-pass", "cell"])
+def test_isothermal_cells_without_a_positive_temperature(path, smooth, otsa):
+    # no rate is defined at T <= 0: such a cell fails every attempt, keeps its
+    # state and raises the cap flag; the other cells are as without it
+    n = (21, 7, 3)
+    rng = np.random.default_rng(11)
+    N, F = random_rad(n, 3, rng)
+    st = {"N": 1e-3 * N, "F": 1e-3 * F, **gas(n, rng)}
+    for k, v in enumerate((0.0, -0.0, -1e4, -1e-300, -1e300)):
+        st["T"][k % 3, 1 + k, 4 * k] = v
+    st["T"][2, 6, 20] = 0.0
+    bad = ~(st["T"] > 0)
+    ctx, o = make_pair(n, (0,) * 6, 3, 0, isothermal=True, smooth=smooth, otsa=otsa, N_floor=1e-12 if smooth else 0.0)
+    ctx.set_transport_path("cell" if path == "cell" else "zmarch")
+    ctx.set_chem_path("auto" if path == "cell" else path)
+    ref, _ = make_pair(n, (0,) * 6, 3, 0, isothermal=True, smooth=smooth, otsa=otsa, N_floor=1e-12 if smooth else 0.0)
+    ok = {**st, "T": np.where(bad, 1e4, st["T"])}
+    for c, s in ((ctx, st), (ref, ok)):
+        c.load_state(s)
+        c.reset_stats()
+        c.step(c.courant_dt(), 1)
+    g, r = ctx.state_numpy(), ref.state_numpy()
+    for k in ("xHII", "xHeII", "xHeIII", "T"):
+        assert np.array_equal(g[k][bad], st[k][bad]), k
+    assert np.all(g["nacc"][bad] == 0) and np.all(g["natt"][bad] == 100000)
+    for k in FIELDS:
+        m = np.broadcast_to(~bad, g[k].shape)
+        assert np.array_equal(g[k][m], r[k][m]), k
+    s = ctx.stats()
+    assert s["flags"] == ref.stats()["flags"] | 1 and s["attempts_max"] == 100000
+    assert not ref.stats()["flags"] & 1
+
+
+def test_isothermal_batch_box_without_a_positive_temperature():
+    from paper_1304_7126_amd.batch import batch_from_specs
+    specs = [ri.BoxSpec(side=9, M=1, nH=1e-2, n_sources=1, seed=5), ri.BoxSpec(side=5, M=3, nH=1e-2, n_sources=1, seed=6)]
+    b, ws, srcs = batch_from_specs(specs, 6.6 * ri.KPC / 128, isothermal=True)
+    b.boxes[1].T[1, 2, 3] = 0.0
+    b.boxes[1].T[4, 4, 4] = -3.0
+    x0 = b.boxes[1].xHII.clone()
+    b.reset_stats()
+    b.step(b.courant_dt(), 1)
+    b.synchronize()
+    s = b.stats()
+    assert s["flags"] == 1 and s["attempts_max"] == 100000
+    assert torch.equal(b.boxes[1].xHII[1, 2, 3], x0[1, 2, 3]) and torch.equal(b.boxes[1].xHII[4, 4, 4], x0[4, 4, 4])
