@@ -245,7 +245,7 @@ hipError_t upload_hll_table(bool fp32, const double *tab, int nf, int nth, void 
 }  // namespace rtm1
 
 // ---------------------------------------------------------------------------
-// Rate tables (rt_rates.h): built once per process and case (7 ms), copied
+// Rate tables (rt_rates.h): built once per process and case (9 ms; case A 14), copied
 // to every context's device.
 // ---------------------------------------------------------------------------
 namespace rtm1 {

@@ -219,7 +219,7 @@ inline void kchem_derive(KChem &k)
 hipError_t upload_hll_table(bool fp32, const double *tab, int nf, int nth, void **out);
 
 // device copy of the rate table of the case in use (freed with hipFree); the
-// host tables are built on first use and kept (0.7 MB)
+// host tables are built on first use and kept (1.2 MB)
 hipError_t upload_rate_table(bool otsa, double **out);
 
 // differentiation form (rt_adjoint.hip)

@@ -79,11 +79,12 @@ constexpr double RT_HEIII_SCALE = 315614.0 / 1263030.0;
 constexpr int RT_SUB = 16;  // intervals per octave
 constexpr int RT_DEG = 9;
 constexpr int RT_COEF = RT_DEG + 1;
-// octaves of the table in global memory, from 2^-40 K to 2^64 K, and of the part of
+// octaves of the table in global memory, from 2^-129 K to 2^64 K, and of the part of
 // it held in LDS, from 2^-3 K to 2^25 K (the HeIII fits read at a quarter of
-// their temperature).  Beyond the global table, where the fits mean nothing,
-// the outermost intervals serve.
-constexpr int RT_XE0 = -40, RT_XNOCT = 104, RT_XNI = RT_XNOCT * RT_SUB;
+// their temperature).  Beyond the global table the outermost intervals serve:
+// above it recombination is 1e-20 of every other rate, below it lie
+// temperatures smaller than a float holds.
+constexpr int RT_XE0 = -129, RT_XNOCT = 193, RT_XNI = RT_XNOCT * RT_SUB;
 constexpr int RT_LE0 = -3, RT_LNOCT = 28, RT_LNI = RT_LNOCT * RT_SUB;
 constexpr int RT_LOFF = (RT_LE0 - RT_XE0) * RT_SUB;  // its first interval
 

@@ -231,3 +231,28 @@ def test_isothermal_batch_box_without_a_positive_temperature():
     s = b.stats()
     assert s["flags"] == 1 and s["attempts_max"] == 100000
     assert torch.equal(b.boxes[1].xHII[1, 2, 3], x0[1, 2, 3]) and torch.equal(b.boxes[1].xHII[4, 4, 4], x0[4, 4, 4])
+
+
+@pytest.mark.parametrize("isothermal", [True, False])
+def test_temperatures_far_below_the_lds_rate_table(isothermal):
+    # 1e-18 to 1e-10 K mean nothing, but they are accepted and the oracle
+    # evaluates the formulas there (without OTSA such gas reaches the attempt
+    # cap on either side, at a count that rounding decides)
+    rng = np.random.default_rng(23)
+    n = (11, 5, 3)
+    N, F = random_rad(n, 3, rng)
+    gs = gas(n, rng)
+    gs["xHII"] = rng.uniform(0.05, 0.9, gs["T"].shape)
+    gs["T"] = 10 ** rng.uniform(-18, -10, gs["T"].shape)
+    st = {"N": 1e-3 * N, "F": 1e-3 * F, **gs}
+    ctxs = []
+    for path in ("two-pass", "one-pass"):
+        ctx, o = make_pair(n, (0,) * 6, 3, 0, isothermal=isothermal)
+        ctx.set_chem_path(path)
+        ctx.load_state(st)
+        ctx.thermochem(ctx.courant_dt())
+        ctxs.append(ctx)
+    compare(*ctxs)
+    fl, nacc, natt = o.thermochem(st, ctxs[0].courant_dt(), want_counts=True)
+    st["nacc"], st["natt"] = nacc, natt
+    chem_compare(ctxs[1].state_numpy(), st)

@@ -148,3 +148,19 @@ def test_exponential(lib):
     y = np.empty_like(z)
     lib.exp_eval(ptr(z), ptr(y), ctypes.c_long(z.size))
     assert np.all(y == 0.0)
+
+
+@pytest.mark.parametrize("case_a", [False, True])
+@pytest.mark.parametrize("fit", range(6))
+def test_table_at_temperatures_no_gas_has(lib, fit, case_a):
+    # down to 2^-126 K (the HeIII fits read at a quarter of it) and up to
+    # 2^64 K a positive temperature has its own rates, within the bounds of
+    # test_table_against_extended_precision
+    rng = np.random.default_rng(9)
+    edges = 2.0 ** np.arange(-126, 64)
+    T = np.concatenate([2.0 ** rng.uniform(-126, 64, 100_000), edges, np.nextafter(edges[1:], 0)])
+    v, d = evaluate(lib, fit, case_a, T)
+    rv, rd = reference(fit, case_a, T)
+    assert np.max(np.abs(v.astype(L) / rv - 1).astype(float)) < 5 * 2.0 ** -53
+    if fit not in (1, 5):
+        assert np.max(np.abs((d.astype(L) - rd) / (rv / T)).astype(float)) < 4e-15
