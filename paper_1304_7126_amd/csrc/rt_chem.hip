@@ -188,7 +188,8 @@ __global__ __launch_bounds__(CHEM_THREADS, CHEM_WAVES) void k_tail(const KChem *
     bool raised = false;
     unsigned rbase = 0, ravail = 0;  // positions this wave has reserved and not yet handed out
     unsigned fl = 0;
-    unsigned a_acc = 0, a_att = 0, a_max = 0;  // of this lane's cells (32 bits outlast a lane's work)
+    unsigned long long a_acc = 0, a_att = 0;  // of this lane's cells (INT_MAX attempts each at most, any number of cells)
+    unsigned a_max = 0;
     __shared__ unsigned s_hist[64];
     if (io.hist) hist_init(s_hist);
     while (true) {
@@ -244,8 +245,8 @@ __global__ __launch_bounds__(CHEM_THREADS, CHEM_WAVES) void k_tail(const KChem *
                 if constexpr (PRE) store_cell_with<R, M>(io, cell, s, T, fpre);
                 else store_cell<R, M>(io, cell, s, T);
                 if (io.hist) hist_add(s_hist, s.acc);
-                a_acc += (unsigned)s.acc;
-                a_att += (unsigned)s.att;
+                a_acc += (unsigned long long)s.acc;
+                a_att += (unsigned long long)s.att;
                 a_max = a_max > (unsigned)s.att ? a_max : (unsigned)s.att;
                 active = false;
             }
@@ -430,7 +431,8 @@ __global__ __launch_bounds__(CHEM_THREADS, CHEM_WAVES) void k_chem_all(const KCh
         }
     };
     unsigned fl = 0, cfl = 0;        // flags of the lane, flags of its current cell
-    unsigned a_acc = 0, a_att = 0, a_max = 0;  // of this lane's cells (32 bits outlast a lane's work)
+    unsigned long long a_acc = 0, a_att = 0;  // of this lane's cells (INT_MAX attempts each at most, any number of cells)
+    unsigned a_max = 0;
     __shared__ unsigned s_hist[64];
     if (io.hist) hist_init(s_hist);
     // the cell's state as the head pass loads it, without the check of its
@@ -487,8 +489,8 @@ __global__ __launch_bounds__(CHEM_THREADS, CHEM_WAVES) void k_chem_all(const KCh
         if constexpr (PRE) store_cell_with<R, M>(io, cell, s, T, fpre);
         else store_cell<R, M>(io, cell, s, T);
         if (io.hist) hist_add(s_hist, s.acc);
-        a_acc += (unsigned)s.acc;
-        a_att += (unsigned)s.att;
+        a_acc += (unsigned long long)s.acc;
+        a_att += (unsigned long long)s.att;
         a_max = a_max > (unsigned)s.att ? a_max : (unsigned)s.att;
     };
     // what a lane without a cell holds: an attempt on it ends at the photon

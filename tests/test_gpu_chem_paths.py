@@ -256,3 +256,20 @@ def test_temperatures_far_below_the_lds_rate_table(isothermal):
     fl, nacc, natt = o.thermochem(st, ctxs[0].courant_dt(), want_counts=True)
     st["nacc"], st["natt"] = nacc, natt
     chem_compare(ctxs[1].state_numpy(), st)
+
+
+def test_attempt_counts_beyond_32_bits_per_lane():
+    # every cell at the cap of INT_MAX attempts (T = 0 held), more than two
+    # cells per persistent lane: the total is exact
+    from paper_1304_7126_amd import RTContext
+    w = ri.lognormal_box(96, 6.6 * 96 / 128, 1, steps=1, seed=1)
+    cap = 2 ** 31 - 1
+    c = RTContext.for_workload(w, fp32=True, isothermal=True, max_attempts=cap)
+    c.load_state(ri.initial_state(w))
+    c.T.zero_()
+    for k in range(2):
+        c.reset_stats()
+        c.thermochem(c.courant_dt())
+        s = c.stats()
+        assert s["attempts_total"] == 96 ** 3 * cap and s["attempts_max"] == cap and s["substeps_total"] == 0
+        assert s["flags"] == 1
