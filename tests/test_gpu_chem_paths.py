@@ -273,3 +273,60 @@ def test_attempt_counts_beyond_32_bits_per_lane():
         s = c.stats()
         assert s["attempts_total"] == 96 ** 3 * cap and s["attempts_max"] == cap and s["substeps_total"] == 0
         assert s["flags"] == 1
+
+
+def warm_state(w, frac, seed):
+    """A restart: frac of the cells ionised and warm, scattered in the first
+    half of the grid's planes and as one block in the rest."""
+    rng = np.random.default_rng(seed)
+    st = ri.initial_state(w)
+    sh = st["T"].shape
+    m = rng.uniform(size=sh) < frac
+    m[sh[0] // 2:] = False
+    m[sh[0] // 2: sh[0] // 2 + int(frac * (sh[0] - sh[0] // 2))] = True
+    st["T"][m] = 10 ** rng.uniform(3.8, 4.4, m.sum())
+    st["xHII"][m] = 0.99
+    st["xHeII"][m] = 0.9
+    st["N"] = np.where(m, 1e-5 * np.array([1.0, 0.5, 0.1]).reshape(3, 1, 1, 1), st["N"])
+    return st
+
+
+@pytest.mark.parametrize("frac", [1.0, 0.26, 0.24, 0.02])
+@pytest.mark.parametrize("fp32,smooth", [(True, False), (False, False), (True, True)])
+def test_first_pass_of_a_warm_state(fp32, smooth, frac):
+    # a state without counts above the lanes of the first fill: warm cells go
+    # to the lists where they are a quarter of their piece or less
+    w, (a, b) = lognormal_pair(52, fp32, 1e-3, smooth=smooth, steps=2)
+    st = warm_state(w, frac, 7)
+    dt = a.courant_dt()
+    for c in (a, b):
+        c.load_state(st)
+        c._bind()
+        c.set_accounting(True)
+        c.step(dt, 2)
+    compare(a, b)
+
+
+def test_first_pass_of_a_warm_state_costs_no_more_than_the_next():
+    # (all warm cells of a state without counts on the lists: 2.9 times)
+    w = ri.lognormal_box(192, 13.2 * 192 / 256, 1, steps=1, seed=2)
+    from paper_1304_7126_amd import RTContext
+    c = RTContext.for_workload(w, fp32=True)
+    c.load_state(warm_state(w, 1.0, 3))
+    keep = [t.clone() for t in (c.N, c.F, c.xHII, c.xHeII, c.xHeIII, c.T)]
+    dt = c.courant_dt()
+    ms = {0: [], 1: []}
+    for _ in range(6):
+        for t, k in zip((c.N, c.F, c.xHII, c.xHeII, c.xHeIII, c.T), keep):
+            t.copy_(k)
+        c._bind()
+        for p in (0, 1):
+            e0, e1 = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            torch.cuda.synchronize()
+            e0.record()
+            c.thermochem(dt)
+            e1.record()
+            torch.cuda.synchronize()
+            ms[p].append(e0.elapsed_time(e1))
+    print(f"# first pass {min(ms[0]):.3f} ms, second {min(ms[1]):.3f} ms", flush=True)
+    assert min(ms[0]) < 1.8 * min(ms[1])
