@@ -322,28 +322,16 @@ __device__ __forceinline__ bool chem_init(const KChem &k, double dt, double T, b
 // call this): 75 KB, without OTSA 113 KB.
 template <int V>
 constexpr int rate_table_len() { return (V & V_CASE_A) ? RTL::len_a : RTL::len_b; }
-__device__ __forceinline__ void copy_columns(gptr src, double *dst, int rows, int sstride, int dstride)
-{
-    // pairs of columns
-    for (int j = threadIdx.x; j < rows * (dstride / 2); j += blockDim.x) {
-        const int r = j / (dstride / 2), c = j - r * (dstride / 2);
-        dst[r * dstride + 2 * c] = src[r * sstride + 2 * c];
-        dst[r * dstride + 2 * c + 1] = src[r * sstride + 2 * c + 1];
-    }
-}
 template <int V>
 __device__ __forceinline__ void rate_table_to_lds(const double *__restrict__ xx, double *l)
 {
-    const gptr x = (gptr)xx;
-    constexpr int o0 = RT_LOFF / RT_SUB;
-    copy_columns(x + RTX::A + RT_LOFF, l + RTL::A, RT_COEF, RT_XNI, RT_LNI);
-    copy_columns(x + RTX::E + RT_LOFF, l + RTL::E, RT_COEF, RT_XNI, RT_LNI);
-    copy_columns(x + RTX::P, l + RTL::P, 1, 0, 2 * RT_COEF * RT_SUB);  // P and Q
-    copy_columns(x + RTX::PO + o0, l + RTL::PO, 2, RT_XNOCT, RT_LNOCT);
-    if constexpr ((V & V_CASE_A) != 0) {
-        copy_columns(x + RTX::DA + RT_LOFF, l + RTL::DA, RT_COEF, RT_XNI, RT_LNI);
-        copy_columns(x + RTX::PB, l + RTL::PB, 1, 0, RT_COEF * RT_SUB);
-        copy_columns(x + RTX::PBO + o0, l + RTL::PBO, 1, 0, RT_LNOCT);
+    constexpr bool CA = (V & V_CASE_A) != 0;
+    const gptr x = (gptr)xx + (CA ? RTX::IA : RTX::IB);
+    constexpr int n = rate_table_len<V>();
+    static_assert(n % 2 == 0, "pairs");
+    for (int j = 2 * (int)threadIdx.x; j < n; j += 2 * (int)blockDim.x) {
+        l[j] = x[j];
+        l[j + 1] = x[j + 1];
     }
     __syncthreads();
 }

@@ -91,18 +91,23 @@ constexpr int RT_LOFF = (RT_LE0 - RT_XE0) * RT_SUB;  // its first interval
 // A table, in doubles: [coefficient][interval] of alpha_HII and of the HII
 // cooling, [coefficient][interval of the mantissa] and [octave] of the powers
 // alpha_HeII and T^-0.397; without OTSA also alpha_A - alpha_B of HII and the
-// case B alpha_HeII.  X: the global table, L: the LDS copy.
+// case B alpha_HeII.  X: the global table, L: the LDS copy, whose image lies
+// behind the global table (IB, without OTSA IA), so that a workgroup's copy is
+// one linear read.
 constexpr int EXP_PAD = 16;
-template <int NI, int NOCT, int EXP>
+template <int NI, int NOCT, int EXP, int IMAGE_B, int IMAGE_A>
 struct RateLayout {
     static constexpr int ni = NI;
     static constexpr int A = 0, E = A + RT_COEF * NI, P = E + RT_COEF * NI, Q = P + RT_COEF * RT_SUB,
-                         PO = Q + RT_COEF * RT_SUB, QO = PO + NOCT, X = QO + NOCT, len_b = X + EXP;
-    static constexpr int DA = len_b, PB = DA + RT_COEF * NI, PBO = PB + RT_COEF * RT_SUB, len_a = PBO + NOCT;
+                         PO = Q + RT_COEF * RT_SUB, QO = PO + NOCT, X = QO + NOCT, end_b = X + EXP;
+    static constexpr int DA = end_b, PB = DA + RT_COEF * NI, PBO = PB + RT_COEF * RT_SUB, end_a = PBO + NOCT;
+    // (images on 16 bytes)
+    static constexpr int IB = (end_b + 1) / 2 * 2, IA = (end_a + 1) / 2 * 2;
+    static constexpr int len_b = IB + IMAGE_B, len_a = IA + IMAGE_A;
 };
 // (X: the exponential's coefficients, in the global table only)
-using RTX = RateLayout<RT_XNI, RT_XNOCT, EXP_PAD>;
-using RTL = RateLayout<RT_LNI, RT_LNOCT, 0>;
+using RTL = RateLayout<RT_LNI, RT_LNOCT, 0, 0, 0>;
+using RTX = RateLayout<RT_XNI, RT_XNOCT, EXP_PAD, RTL::len_b, RTL::len_a>;
 
 // coefficients of the exponential (exp_neg)
 constexpr int EXP_COEF = 10;
@@ -213,6 +218,21 @@ inline void build_rate_table(bool case_a, double *tab)
     for (int m = 0; m < EXP_PAD; ++m) tab[RTX::X + m] = m < EXP_COEF ? EXP_C[m] : 0.0;
     build_power(rate_fit(RF_T397, case_a), tab + RTX::Q, tab + RTX::QO);
     if (case_a) build_power(rate_fit(RF_AHEII, false), tab + RTX::PB, tab + RTX::PBO);
+    // the image of the LDS copy
+    double *l = tab + (case_a ? RTX::IA : RTX::IB);
+    auto rows = [&](int src, int dst, int n, int sstride, int dstride) {
+        for (int r = 0; r < n; ++r) memcpy(l + dst + r * dstride, tab + src + r * sstride, dstride * sizeof(double));
+    };
+    constexpr int o0 = RT_LOFF / RT_SUB;
+    rows(RTX::A + RT_LOFF, RTL::A, RT_COEF, RT_XNI, RT_LNI);
+    rows(RTX::E + RT_LOFF, RTL::E, RT_COEF, RT_XNI, RT_LNI);
+    rows(RTX::P, RTL::P, 1, 0, 2 * RT_COEF * RT_SUB);  // P and Q
+    rows(RTX::PO + o0, RTL::PO, 2, RT_XNOCT, RT_LNOCT);
+    if (case_a) {
+        rows(RTX::DA + RT_LOFF, RTL::DA, RT_COEF, RT_XNI, RT_LNI);
+        rows(RTX::PB, RTL::PB, 1, 0, RT_COEF * RT_SUB);
+        rows(RTX::PBO + o0, RTL::PBO, 1, 0, RT_LNOCT);
+    }
 }
 
 // -------------------------------------------------------------- evaluation
