@@ -50,6 +50,7 @@ struct rt_ctx {
     RedOut *dred = nullptr;
     unsigned qcap = 0;               // chemistry queue capacity (cells)
     unsigned qcap_max = 0;           // capacity the scratch size is computed for
+    bool order_only = false;         // scratch laid out for the one pass's order, without a queue (rt_step_noalloc)
     int head_attempts = HEAD_ATTEMPTS;
     int chem_path = RT_CHEM_AUTO;     // chemistry after a separate transport: one pass or head + tail
     // kernel arrangement of the transport (rt_set_transport_path) and the
@@ -532,7 +533,7 @@ static size_t acct_region(const rt_ctx *c)
 
 static size_t scratch_need(const rt_ctx *c)
 {
-    return ((reduction_scratch_bytes() + 255) & ~(size_t)255) + queue_bytes(c->qcap_max, c->params.smooth != 0) +
+    return ((reduction_scratch_bytes() + 255) & ~(size_t)255) + queue_bytes(c->qcap_max, c->params.smooth != 0, c->order_only) +
            acct_region(c) + prev_att_bytes(c) + src_map_bytes(c);
 }
 
@@ -540,7 +541,7 @@ static size_t scratch_need(const rt_ctx *c)
 static double *acct_part(const rt_ctx *c)
 {
     return (double *)((char *)c->st.scratch + ((reduction_scratch_bytes() + 255) & ~(size_t)255) +
-                      queue_bytes(c->qcap_max, c->params.smooth != 0));
+                      queue_bytes(c->qcap_max, c->params.smooth != 0, c->order_only));
 }
 
 // previous-pass attempt counts: after the accounting partials
@@ -969,7 +970,8 @@ extern "C" rt_status rt_step(rt_ctx *c, double dt, int nsteps)
 
 // rt_step in the device's static scratch array: the same launches with the
 // reduction partials, the chemistry queue (of the capacity that fits; cells
-// beyond it finish in the first pass, which leaves results unchanged), the
+// beyond it finish in the first pass, which leaves results unchanged) or the
+// one pass's order (where it fits; else the cells are taken in grid order), the
 // accounting partials and the previous-pass attempt counts laid out there.
 extern "C" rt_status rt_step_noalloc(rt_ctx *c, double dt, int nsteps)
 {
@@ -993,6 +995,11 @@ extern "C" rt_status rt_step_noalloc(rt_ctx *c, double dt, int nsteps)
     const size_t spare = NOALLOC_SCRATCH_BYTES - fixed;
     size_t cap = spare > 512 ? (spare - 512) / queue_cell_bytes(false) : 0;
     if (cap > c->grid.ncell) cap = c->grid.ncell;
+    // the one pass needs its order of every cell (12 bytes each) and no queue
+    const unsigned nc = (unsigned)c->grid.ncell;
+    const bool order_only =
+        use_zmarch(c) && use_one_pass(c) && queue_bytes(nc, false, true) - queue_bytes(0, false) <= spare;
+    if (order_only) cap = nc;
     // swap the static layout in (no timing: its events would be created)
     void *save_scr = c->st.scratch;
     const size_t save_bytes = c->st.scratch_bytes;
@@ -1000,6 +1007,7 @@ extern "C" rt_status rt_step_noalloc(rt_ctx *c, double dt, int nsteps)
     c->st.scratch = ptr;
     c->st.scratch_bytes = NOALLOC_SCRATCH_BYTES;
     c->qcap = c->qcap_max = (unsigned)cap;
+    c->order_only = order_only;
     c->timing = false;
     if (scratch_need(c) > NOALLOC_SCRATCH_BYTES) {
         r = RT_EINVAL;
@@ -1020,6 +1028,7 @@ extern "C" rt_status rt_step_noalloc(rt_ctx *c, double dt, int nsteps)
     c->st.scratch_bytes = save_bytes;
     c->qcap = save_cap;
     c->qcap_max = save_max;
+    c->order_only = false;
     c->timing = save_timing;
     return r;
 }

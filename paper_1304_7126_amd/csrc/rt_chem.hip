@@ -611,7 +611,7 @@ static void launch_M(ChemPass pass, const ChemCall<R> &a, hipStream_t s)
     // without the order: one counter for every wave, so more at a time
     const unsigned chunk = more && !ordered ? CHEM_SWEEP_CHUNK : 64u;
     QueueView qa = a.q;
-    qa.slab = ordered ? (unsigned *)a.q.v : a.q.head;
+    if (!ordered) qa.slab = a.q.head;
     // (with at most one cell per lane the one pass hands out its first widths
     // only and uses no counter: 4.5 us of a 16^3 step's 63)
     if (pass != CHEM_TAIL && (more || pass != CHEM_ALL))

@@ -163,8 +163,9 @@ struct ChemIO {
 constexpr int HEAD_ATTEMPTS = 3;
 
 // bytes of scratch for a queue of cap cells (after the reduction partials),
-// laid out for smoothed RT when smooth is set
-size_t queue_bytes(unsigned cap, bool smooth);
+// laid out for smoothed RT when smooth is set; order_only: for the one pass's
+// order of cap cells, without their states
+size_t queue_bytes(unsigned cap, bool smooth, bool order_only = false);
 // bytes one queued cell takes (without the alignment of the layout)
 size_t queue_cell_bytes(bool smooth);
 // cap: cells the kernels may queue; layout_cap: capacity the scratch is laid out for

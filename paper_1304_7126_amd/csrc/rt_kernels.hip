@@ -248,12 +248,15 @@ size_t reduction_scratch_bytes() { return (size_t)RED_BLOCKS * sizeof(RedOut); }
 
 // scratch layout: [reduction partials][queue counters, 512 B]
 //                 [cell, acc, att: 3 x cap int32][QV_GRID (or QV_SMOOTH) x cap doubles]
+// (the one-pass chemistry holds its order in the int32 planes and its slab
+// counters behind them; order_only lays out nothing else)
 static size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 
-size_t queue_bytes(unsigned cap, bool smooth)
+size_t queue_bytes(unsigned cap, bool smooth, bool order_only)
 {
     return 512 + align256((size_t)cap * 3 * sizeof(int32_t)) +
-           (size_t)(smooth ? QV_SMOOTH : QV_GRID) * cap * sizeof(double);
+           (order_only ? CHEM_XCDS * QUEUE_SLAB_STRIDE * sizeof(unsigned)
+                       : (size_t)(smooth ? QV_SMOOTH : QV_GRID) * cap * sizeof(double));
 }
 
 size_t queue_cell_bytes(bool smooth) { return 3 * sizeof(int32_t) + (size_t)(smooth ? QV_SMOOTH : QV_GRID) * sizeof(double); }
@@ -264,7 +267,6 @@ QueueView queue_view(void *scratch, unsigned cap, unsigned layout_cap)
     QueueView q;
     q.count = (unsigned *)b;
     q.head = q.count + 1;
-    q.slab = q.head;
     q.cnt[0] = q.count + 64;
     q.cnt[1] = q.count + 32;
     q.cnt[2] = q.count;
@@ -274,6 +276,7 @@ QueueView queue_view(void *scratch, unsigned cap, unsigned layout_cap)
     q.att = q.acc + layout_cap;
     b += align256((size_t)layout_cap * 3 * sizeof(int32_t));
     q.v = (double *)b;
+    q.slab = (unsigned *)b;
     q.cap = cap;
     q.rbeg[0] = 0;
     q.rlen[0] = cap / 16;

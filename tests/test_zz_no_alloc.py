@@ -45,6 +45,45 @@ def test_step_noalloc_equals_step_on_two_calls(fp32, path):
         assert int(gb["natt"].max()) > 10  # cells subcycled (the queue was used)
 
 
+@pytest.mark.parametrize("n,steps", [(60, 4), (96, 4), (176, 2)])
+def test_step_noalloc_equals_step_above_one_cell_per_lane(n, steps):
+    # 216,000 and 884,736 cells: taken in the one pass's order, which the array
+    # holds for them without a queue; 5,451,776: too many for the array, taken
+    # in grid order from one counter
+    w, (ref, na) = ctx_pair(n, True, "auto", max(3, n // 6))
+    dt = ref.courant_dt()
+    print(f"# noalloc {n}^3", flush=True)
+    ref.step(dt, steps)
+    na.step_noalloc(dt, steps)
+    assert ref.current == na.current
+    for k in ("N", "F", "xHII", "xHeII", "xHeIII", "T", "nacc", "natt"):
+        assert torch.equal(getattr(ref, k), getattr(na, k)), (n, k)
+    assert int(na.natt.max()) > 20
+
+
+def test_step_noalloc_takes_the_order_of_step():
+    # four steps of a state with I-fronts, each call without attempt counts:
+    # the same launches as rt_step's (without the order 1.17 times as long)
+    w, (ref, na) = ctx_pair(96, True, "auto", 75)
+    dt = ref.courant_dt()
+    us = {0: [], 1: []}
+    for k in range(16):
+        for j, c in enumerate((ref, na)):
+            e0, e1 = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            if j == 0:
+                c._bind()  # (an even number of steps: set 0 is the current one)
+            torch.cuda.synchronize()
+            e0.record()
+            (c.step if j == 0 else c.step_noalloc)(dt, 4)
+            e1.record()
+            torch.cuda.synchronize()
+            us[j].append(1e3 * e0.elapsed_time(e1))
+    a, b = (min(us[j][8:]) for j in (0, 1))
+    print(f"# four steps: rt_step {a:.0f} us, rt_step_noalloc {b:.0f} us", flush=True)
+    assert torch.equal(ref.xHII, na.xHII) and torch.equal(ref.N, na.N)
+    assert b < 1.12 * a
+
+
 def test_step_noalloc_refuses_what_it_cannot_hold():
     from paper_1304_7126_amd import RTContext
     from paper_1304_7126_amd.capi import RTError
