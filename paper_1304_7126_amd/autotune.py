@@ -3,12 +3,15 @@
 It times candidate launch configurations on the caller's own workload (the
 state is snapshotted and restored between candidates, so the tuning leaves
 the simulation untouched; results never depend on the configuration) and
-caches the winner in a JSON file keyed by a signature of the workload and the
-GPU.  Tunables: for the single-grid step, the chemistry attempts per cell in
-the fused first pass; for the batched step, also the persistent head grid
-(blocks per compute unit) and the tail grid."""
+caches the winner in a JSON file keyed by a signature of the workload, the
+GPU and the built library (a winner among other kernels says nothing about
+these).  Tunables: for the single-grid step, where its chemistry runs as a
+head pass and a tail (the per-cell transport path, or two passes asked for),
+the attempts per cell in the head pass; for the batched step, also the
+persistent head grid (blocks per compute unit) and the tail grid."""
 from __future__ import annotations
 
+import functools
 import hashlib
 import itertools
 import json
@@ -16,6 +19,8 @@ import os
 import time
 
 import torch
+
+from .capi import LIB_PATH
 
 CACHE = os.environ.get("RTM1_TUNE_CACHE", os.path.join(os.path.expanduser("~"), ".cache", "rtm1_tune.json"))
 
@@ -45,9 +50,15 @@ def _gpu_name():
         return "unknown"
 
 
+@functools.lru_cache(maxsize=None)
+def _library_digest(path):
+    with open(path, "rb") as f:
+        return hashlib.sha1(f.read()).hexdigest()
+
+
 def batch_signature(batch):
     shapes = sorted((b.n, b.M) for b in batch.boxes)
-    h = hashlib.sha1(json.dumps([shapes, batch.fp32, _gpu_name()]).encode()).hexdigest()[:16]
+    h = hashlib.sha1(json.dumps([shapes, batch.fp32, _gpu_name(), _library_digest(LIB_PATH)]).encode()).hexdigest()[:16]
     return "batch:" + h
 
 
