@@ -306,6 +306,10 @@ rt_status rt_set_chem_path(rt_ctx *ctx, int path);
  * fit finish in the first pass).  Negative values keep the current one. */
 rt_status rt_set_tuning(rt_ctx *ctx, int head_attempts, long long queue_cap);
 
+/* The head_attempts rt_step runs with, or -1 when its chemistry has no such
+ * first pass (one pass after the z-marching transport). */
+int rt_head_attempts(const rt_ctx *ctx);
+
 /* Diagnostics of the current state and accumulated counters; synchronises
  * the stream.  Needs a bound scratch buffer. */
 rt_status rt_get_stats(rt_ctx *ctx, rt_stats *out);

@@ -99,7 +99,11 @@ def tune_batch(batch, dt, trial_steps=3, head_blocks=(2, 4, 8), head_attempts=(1
 
 def tune_grid(ctx, dt, trial_steps=3, head_attempts=(1, 2, 3, 4, 6), verbose=False):
     """Pick the fastest head_attempts for a single-grid context (state is
-    restored afterwards)."""
+    restored afterwards).  Where rt_step runs no head pass there is nothing to
+    time: head_attempts -1 (which set_tuning takes as "keep") and no trials."""
+    from .capi import lib
+    if lib().rt_head_attempts(ctx._h) < 0:
+        return {"head_attempts": -1, "trials": []}
     torch.cuda.synchronize()
     saved = [t.clone() for t in (ctx.N, ctx.F, ctx.xHII, ctx.xHeII, ctx.xHeIII, ctx.T)]
     cur = ctx.current
@@ -107,7 +111,6 @@ def tune_grid(ctx, dt, trial_steps=3, head_attempts=(1, 2, 3, 4, 6), verbose=Fal
     for K in head_attempts:
         for t, s in zip((ctx.N, ctx.F, ctx.xHII, ctx.xHeII, ctx.xHeIII, ctx.T), saved):
             t.copy_(s)
-        from .capi import lib
         lib().rt_set_current(ctx._h, cur)
         ctx.set_tuning(K, -1)
         torch.cuda.synchronize()
@@ -119,7 +122,6 @@ def tune_grid(ctx, dt, trial_steps=3, head_attempts=(1, 2, 3, 4, 6), verbose=Fal
             print(f"  tune K={K}: {res[-1][0] * 1e3:.3f} ms/step", flush=True)
     for t, s in zip((ctx.N, ctx.F, ctx.xHII, ctx.xHeII, ctx.xHeIII, ctx.T), saved):
         t.copy_(s)
-    from .capi import lib
     lib().rt_set_current(ctx._h, cur)
     res.sort()
     ctx.set_tuning(res[0][1], -1)

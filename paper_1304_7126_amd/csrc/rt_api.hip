@@ -835,6 +835,11 @@ static SmoothArgs smooth_args(const rt_ctx *c, int pre_set, bool injected)
 // there).
 static bool use_one_pass(const rt_ctx *c) { return c->chem_path != RT_CHEM_TWO_PASS; }
 
+extern "C" int rt_head_attempts(const rt_ctx *c)
+{
+    return c && !(use_zmarch(c) && use_one_pass(c)) ? c->head_attempts : -1;
+}
+
 static rt_status do_chem(rt_ctx *c, double dt)
 {
     SmoothArgs sa;
