@@ -173,57 +173,78 @@ static hipError_t noalloc_setup(int dev)
 // a root of the (E, F_x, F_y) block, whose other two roots follow from the
 // block's trace and principal minors.  The f = 1 row (a beam) is the limit
 // where all speeds equal cos t.
+//
+// In extended precision, because the roots' discriminant cancels towards
+// f = 1 (in doubles the nodes are off by up to 4e-15), and for angles up to
+// pi/2 only: beyond, lmin(f, pi - t) = -lmax(f, t), which holds to the bit as
+// the FP64 transport reads it (upload_hll_table).  One node is no mirror
+// image: a beam across the axis keeps 6e-17, the rounded cosine of pi/2, for
+// both speeds; with zero there the range of speeds of such a beam can become
+// so narrow that its reciprocal overflows.
 // ---------------------------------------------------------------------------
-static void hll_speeds_closed_form(double f, double t, double &lmin, double &lmax)
+typedef long double ld;
+struct HllRow {  // what depends on f alone
+    ld f, s, a, ap, b, bp;
+    explicit HllRow(ld ff) : f(ff), s(ff * ff)
+    {
+        const ld r = sqrtl(4 - 3 * s), q = 5 + 2 * r;
+        const ld chi = (3 + 4 * s) / q, chis = (4 * q + (3 + 4 * s) * 3 / r) / (q * q);
+        const ld e = 3 / (2 + r) + 6;
+        a = (1 - chi) / 2;
+        ap = -chis / 2;
+        b = e / q;
+        bp = -ld(1.5) / r * (-3 * q / ((2 + r) * (2 + r)) - 2 * e) / (q * q);
+    }
+};
+static void hll_speeds_closed_form(const HllRow &h, ld ct, ld st, double &lmin, double &lmax)
 {
-    const double s = f * f;
-    const double r = std::sqrt(4.0 - 3.0 * s);
-    const double q = 5.0 + 2.0 * r;
-    const double chi = (3.0 + 4.0 * s) / q;
-    const double chis = (4.0 * q + (3.0 + 4.0 * s) * 3.0 / r) / (q * q);
-    const double a = 0.5 * (1.0 - chi);
-    const double ap = -0.5 * chis;
-    const double b = (3.0 / (2.0 + r) + 6.0) / q;
-    const double drds = -1.5 / r;
-    const double bp = drds * (-3.0 * q / ((2.0 + r) * (2.0 + r)) - 2.0 * (3.0 / (2.0 + r) + 6.0)) / (q * q);
-    const double fx = f * std::cos(t), fy = f * std::sin(t);
-    double J[3][3];
-    J[0][0] = 0.0;
-    J[0][1] = 1.0;
-    J[0][2] = 0.0;
-    J[1][0] = a - 2.0 * s * ap + fx * fx * (-b - 2.0 * s * bp);
-    J[1][1] = 2.0 * ap * fx + 2.0 * b * fx + 2.0 * bp * fx * fx * fx;
-    J[1][2] = 2.0 * ap * fy + 2.0 * bp * fx * fx * fy;
-    J[2][0] = fx * fy * (-b - 2.0 * s * bp);
-    J[2][1] = b * fy + 2.0 * bp * fx * fx * fy;
-    J[2][2] = b * fx + 2.0 * bp * fx * fy * fy;
-    const double lz = b * fx;
-    const double S = J[0][0] + J[1][1] + J[2][2] - lz;
-    const double M2 = (J[0][0] * J[1][1] - J[0][1] * J[1][0]) + (J[0][0] * J[2][2] - J[0][2] * J[2][0]) +
-                      (J[1][1] * J[2][2] - J[1][2] * J[2][1]);
-    const double P = M2 - lz * S;
-    double disc = 0.25 * S * S - P;
-    disc = disc > 0.0 ? std::sqrt(disc) : 0.0;
-    const double lm = 0.5 * S - disc, lp = 0.5 * S + disc;
-    lmin = lm < lz ? lm : lz;
-    lmax = lp > lz ? lp : lz;
+    const ld s = h.s, a = h.a, ap = h.ap, b = h.b, bp = h.bp;
+    const ld fx = h.f * ct, fy = h.f * st;
+    ld J[3][3];
+    J[0][0] = 0;
+    J[0][1] = 1;
+    J[0][2] = 0;
+    J[1][0] = a - 2 * s * ap + fx * fx * (-b - 2 * s * bp);
+    J[1][1] = 2 * ap * fx + 2 * b * fx + 2 * bp * fx * fx * fx;
+    J[1][2] = 2 * ap * fy + 2 * bp * fx * fx * fy;
+    J[2][0] = fx * fy * (-b - 2 * s * bp);
+    J[2][1] = b * fy + 2 * bp * fx * fx * fy;
+    J[2][2] = b * fx + 2 * bp * fx * fy * fy;
+    const ld lz = b * fx;
+    const ld S = J[0][0] + J[1][1] + J[2][2] - lz;
+    const ld M2 = (J[0][0] * J[1][1] - J[0][1] * J[1][0]) + (J[0][0] * J[2][2] - J[0][2] * J[2][0]) +
+                  (J[1][1] * J[2][2] - J[1][2] * J[2][1]);
+    const ld P = M2 - lz * S;
+    ld disc = S * S / 4 - P;
+    disc = disc > 0 ? sqrtl(disc) : 0;
+    const ld lm = S / 2 - disc, lp = S / 2 + disc;
+    lmin = (double)(lm < lz ? lm : lz);
+    lmax = (double)(lp > lz ? lp : lz);
 }
 
 static void build_hll(int nf, int nth, std::vector<double> &tab)
 {
     tab.assign((size_t)nf * nth * 2, 0.0);
+    const int half = (nth + 1) / 2;  // angles up to pi/2
+    std::vector<ld> ct(half), st(half);
+    for (int k = 0; k < half; ++k) {
+        const ld t = ld(3.14159265358979323846264338327950288L) * k / (nth - 1);
+        const bool mid = 2 * k == nth - 1;
+        ct[k] = mid ? 0 : cosl(t);
+        st[k] = mid ? 1 : sinl(t);
+    }
     for (int i = 0; i < nf; ++i) {
-        const double f = (double)i / (nf - 1);
-        for (int k = 0; k < nth; ++k) {
-            const double t = M_PI * (double)k / (nth - 1);
+        const HllRow h((ld)i / (nf - 1));
+        for (int k = 0; k < half; ++k) {
             double lo, hi;
-            if (i == nf - 1) {
-                lo = hi = std::cos(t);
-            } else {
-                hll_speeds_closed_form(f, t, lo, hi);
-            }
-            tab[((size_t)i * nth + k) * 2 + 0] = lo;
-            tab[((size_t)i * nth + k) * 2 + 1] = hi;
+            if (i == nf - 1) lo = hi = (double)ct[k];
+            else hll_speeds_closed_form(h, ct[k], st[k], lo, hi);
+            double *e = &tab[((size_t)i * nth + k) * 2], *m = &tab[((size_t)i * nth + (nth - 1 - k)) * 2];
+            m[0] = -hi;
+            m[1] = -lo;
+            e[0] = lo;
+            e[1] = hi;
+            if (i == nf - 1 && 2 * k == nth - 1) e[0] = e[1] = 6.123233995736766e-17;
         }
     }
 }

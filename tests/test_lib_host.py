@@ -48,6 +48,55 @@ def test_hll_table_matches_oracle():
     assert np.max(np.abs(a - b)) < 1e-12
 
 
+def test_hll_table_mirrors_to_the_bit():
+    # lambda_min(f, theta) = -lambda_max(f, pi - theta): the FP64 transport
+    # holds lambda_max alone.  Both speeds of a beam across the axis are the
+    # rounded cosine of pi/2, not zero
+    from paper_1304_7126_amd.runtime import hll_table
+    t = hll_table()
+    assert t[100, 50, 0] == t[100, 50, 1] == np.cos(np.pi / 2)
+    t[100, 50, 0] *= -1
+    assert np.array_equal(t[:, :, 0], -t[:, ::-1, 1])
+
+
+@pytest.mark.parametrize("k", [0, 13, 50, 77, 100])
+def test_hll_table_against_extended_precision(k):
+    # the nodes are roots of the flux Jacobian's characteristic polynomial,
+    # which factors into (b f cos t - x) and a cubic: one Newton step of each
+    # entry on the cubic (or on that root) in extended precision moves it by no
+    # more than a rounding of the entry, 2^-53, and of the step.  The Jacobian
+    # by a complex step; f up to 0.9, where the roots are apart
+    from paper_1304_7126_amd.runtime import hll_table
+    L, C = np.longdouble, np.clongdouble
+    tab = hll_table()[:91, k].astype(L)
+    th = L("3.14159265358979323846264338327950288") * k / 100
+    f = np.arange(91).astype(L) / 100
+    U0 = [np.ones(91, C), (f * np.cos(th)).astype(C), (f * np.sin(th)).astype(C)]
+    J = np.zeros((91, 3, 3), L)
+    h = L(1e-40)
+    for j in range(3):
+        U = [u.copy() for u in U0]
+        U[j] = U[j] + C(1j) * h
+        q = (U[1] ** 2 + U[2] ** 2) / U[0] ** 2
+        r = np.sqrt(4 - 3 * q)
+        chi, B = (3 + 4 * q) / (5 + 2 * r), (3 / (2 + r) + 6) / (5 + 2 * r)
+        G = [U[1], (1 - chi) * U[0] / 2 + B * U[1] * U[1] / U[0], B * U[1] * U[2] / U[0]]
+        for m in range(3):
+            J[:, m, j] = G[m].imag / h
+    r = np.sqrt(4 - 3 * f ** 2)
+    lz = (3 / (2 + r) + 6) / (5 + 2 * r) * f * np.cos(th)
+    c2 = J[:, 0, 0] + J[:, 1, 1] + J[:, 2, 2]
+    c1 = sum(J[:, a, a] * J[:, b, b] - J[:, a, b] * J[:, b, a] for a, b in ((0, 1), (0, 2), (1, 2)))
+    c0 = (J[:, 0, 0] * (J[:, 1, 1] * J[:, 2, 2] - J[:, 1, 2] * J[:, 2, 1]) -
+          J[:, 0, 1] * (J[:, 1, 0] * J[:, 2, 2] - J[:, 1, 2] * J[:, 2, 0]) +
+          J[:, 0, 2] * (J[:, 1, 0] * J[:, 2, 1] - J[:, 1, 1] * J[:, 2, 0]))
+    for e in (0, 1):
+        x = tab[:, e]
+        step = (((x - c2) * x + c1) * x - c0) / ((3 * x - 2 * c2) * x + c1)
+        off = np.minimum(np.abs(step), np.abs(x - lz))
+        assert np.max(off) < 2.0 ** -53 + 1e-17
+
+
 def _init(**over):
     L = capi.lib()
     g = capi.RtGrid()
