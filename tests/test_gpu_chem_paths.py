@@ -5,8 +5,10 @@ in a persistent tail): the same bits in every field and the same counters,
 for both precisions, one to three groups, smoothed RT and the case without
 the on-the-spot approximation, over several steps of the split rt_step and
 for rt_thermochem alone; with non-finite cells; with a list of long chains
-larger than the room it has; and on a grid large enough (over the 262,144
-lanes of the first fill) that most cells reach their lane as a refill."""
+larger than the room it has; and on a grid large enough (over the 131,072
+lanes of the first fill) that most cells reach their lane as a refill.  The
+order and the lists are in use above 131,072 cells, one per lane of the first
+fill; the smaller grids here take their cells in grid order."""
 import numpy as np
 import pytest
 import torch
@@ -330,3 +332,64 @@ def test_first_pass_of_a_warm_state_costs_no_more_than_the_next():
             ms[p].append(e0.elapsed_time(e1))
     print(f"# first pass {min(ms[0]):.3f} ms, second {min(ms[1]):.3f} ms", flush=True)
     assert min(ms[0]) < 1.8 * min(ms[1])
+
+
+@pytest.mark.parametrize("M,fp32,iso,smooth,otsa,cap", [
+    (1, True, False, False, True, None), (2, False, False, False, True, None), (1, False, True, False, True, None),
+    (3, True, True, False, True, None), (2, True, False, True, False, None), (3, False, False, True, False, 7)])
+def test_sorted_pieces_of_every_variant(M, fp32, iso, smooth, otsa, cap):
+    # 53 x 51 x 50 = 135,150 cells: ordered, with lists from the second step on
+    # (gas of one class when it is isothermal), against the two passes
+    from paper_1304_7126_amd import RTContext
+    w = ri.lognormal_box(53, 6.6 * 53 / 128, 6, steps=4, seed=9,
+                         spectrum=ri.Spectrum(kind="bb", T_bb=1e5, edges_eV={1: ri.EDGES_1, 2: ri.EDGES_2, 3: ri.EDGES_3}[M]))
+    w.nH_mean, w.otsa = 0.1, otsa
+    st = ri.initial_state(w)
+    w.n = (53, 51, 50)
+    st = {k: np.ascontiguousarray(v[..., :50, :51, :]) for k, v in st.items()}
+    if iso:
+        st["T"][:] = 1e4
+    ijk, nd = ri.random_sources(w.n, w.n_sources, w.seed)
+    ctxs = []
+    for path in ("two-pass", "one-pass"):
+        c = RTContext.for_workload(w, fp32=fp32, counters=True, smooth=smooth, isothermal=iso, N_floor=1e-12 if smooth else 0.0)
+        c.load_state(st)
+        c.set_sources(ijk, c.source_rates(nd))
+        c.set_chem_path(path)
+        c.set_accounting(True)
+        if cap is not None:
+            c.set_tuning(-1, cap)
+        c.reset_stats()
+        c.step(c.courant_dt(), w.steps)
+        ctxs.append(c)
+    s = compare(*ctxs)
+    listed = int((ctxs[1].natt >= 20).sum())
+    print(f"# M={M} fp32={fp32} iso={iso} smooth={smooth} otsa={otsa}: {listed} cells of 20 attempts or more", flush=True)
+    assert listed > 0 and s["attempts_max"] >= 20
+
+
+@pytest.mark.parametrize("lo,hi", [(-2.0, 0.5), (0.9, 1.3), (7.2, 7.8), (7.5, 10.0)])
+def test_case_a_at_the_ends_of_the_lds_rate_table(lo, hi):
+    # the emission's difference of two rates and the case A cooling from global
+    # memory in lanes outside the LDS copy: one pass (LDS) and two passes (the
+    # head pass reads all from global memory) bit for bit; the oracle where the
+    # substeps do not end at the cap (cold gas without OTSA does)
+    rng = np.random.default_rng(int(10 * (hi + 20)))
+    n = (24, 17, 9)
+    N, F = random_rad(n, 3, rng)
+    gs = gas(n, rng)
+    gs["T"] = 10 ** rng.uniform(lo, hi, gs["T"].shape)
+    st = {"N": 1e-3 * N, "F": 1e-3 * F, **gs}
+    ctxs = []
+    for path in ("two-pass", "one-pass"):
+        ctx, o = make_pair(n, (0,) * 6, 3, 0, otsa=False)
+        ctx.set_chem_path(path)
+        ctx.load_state(st)
+        ctx.thermochem(ctx.courant_dt())
+        ctxs.append(ctx)
+    compare(*ctxs)
+    if lo < 7.0:
+        return
+    fl, nacc, natt = o.thermochem(st, ctxs[0].courant_dt(), want_counts=True)
+    st["nacc"], st["natt"] = nacc, natt
+    chem_compare(ctxs[1].state_numpy(), st)
