@@ -279,12 +279,9 @@ __device__ __forceinline__ void head_chunk(const BoxDev &b, const KChem &k, uint
         }
         if (!__syncthreads_or(want && p == ~0u)) break;
     }
-    const bool queued = p != ~0u;
-    if (queued) bq_store(q, stride, p, box, i, s);
-    if (want && !queued) {
-        while (!done) done = chem_attempt<CM>(k, rx, rt, cc, s, fl);
-    }
-    if (valid && !queued) {
+    // (the regions together hold every cell, so one of the three has room)
+    if (p != ~0u) bq_store(q, stride, p, box, i, s);
+    if (valid && done) {
         const double T = chem_finish<CM>(k, cc, s, fl);
         bstore<R>(b, dst, i, s, T, fo);
         a_acc += (unsigned long long)s.acc;
