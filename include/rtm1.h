@@ -260,11 +260,13 @@ rt_status rt_step(rt_ctx *ctx, double dt, int nsteps);
  * device memory (code under HIP graph capture, tight serving loops,
  * harnesses that forbid allocation): the state must be bound (rt_bind
  * accepts scratch = NULL, scratch_bytes = 0), and the reduction partials,
- * the chemistry queue, the accounting partials and the previous pass's
- * attempt counts go to a static device array of 64 MiB that the library
- * holds on every GPU it runs on until the process ends.  The queue takes
- * what the array has left (cells beyond it finish in the first chemistry
- * pass); results are the bits rt_step gives.  Allocates nothing and makes
+ * the chemistry's queue or order of the cells, the accounting partials and
+ * the previous pass's attempt counts go to a static device array of 64 MiB
+ * that the library holds on every GPU it runs on until the process ends.
+ * The queue of two passes takes what the array has left (cells beyond it
+ * finish in the first one), the one pass's order 12 bytes per cell where
+ * they fit (else cells are taken in grid order); results are the bits
+ * rt_step gives.  Allocates nothing and makes
  * no timing events.  RT_EINVAL when the grid needs more than the array
  * (about 1 + 48/256 bytes per cell besides the queue: up to ~56 M cells),
  * RT_EUNSUPPORTED with smooth = 1.  Every call on a GPU shares its array and
@@ -280,7 +282,7 @@ rt_status rt_step_noalloc(rt_ctx *ctx, double dt, int nsteps);
  *   RT_PATH_ZMARCH  workgroups march x-row tiles through z, evaluating each
  *                   cell's closure and wave speeds once and passing them to
  *                   the faces through LDS and registers; rt_step runs it,
- *                   then the chemistry passes.  Needs nx <= 1024 (FP32
+ *                   then the chemistry passes.  Needs nx <= 768 (FP32
  *                   transport) or nx <= 512 (FP64): RT_EINVAL otherwise. */
 enum { RT_PATH_AUTO = 0, RT_PATH_CELL = 1, RT_PATH_ZMARCH = 2 };
 rt_status rt_set_transport_path(rt_ctx *ctx, int path);

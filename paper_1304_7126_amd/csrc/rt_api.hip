@@ -1064,7 +1064,7 @@ extern "C" rt_status rt_set_transport_path(rt_ctx *c, int path)
     if (!c) return RT_EINVAL;
     if (path < RT_PATH_AUTO || path > RT_PATH_ZMARCH) RT_FAIL(c, RT_EINVAL, "path must be RT_PATH_AUTO, _CELL or _ZMARCH");
     if (path == RT_PATH_ZMARCH && !transport_z_fits(c->fp32, c->grid))
-        RT_FAIL(c, RT_EINVAL, "the z-marching transport needs nx <= %d", c->fp32 ? 1024 : 512);
+        RT_FAIL(c, RT_EINVAL, "the z-marching transport needs nx <= %d", c->fp32 ? 768 : 512);
     c->path = path;
     return RT_OK;
 }

@@ -26,11 +26,13 @@ __device__ __forceinline__ void hist_flush(const unsigned *sh, unsigned long lon
 // (all groups, source set -> registers); then up to K chemistry attempts.
 // Cells that finish are written to the destination arrays; the rest go to
 // the queue (or, when it is full, finish in place).
-// Waves per SIMD the head kernel is compiled for: three (168 VGPRs, a few
-// bytes of spill) measured faster than two without spills, also for the
-// FP64 three-group variant (191 VGPRs at two waves: 8.7 -> 7.9 ms per head
-// launch at 256^3 x 3 once multiply-adds fuse per expression) and for the
-// smoothed one (140 bytes of spill at three: 6.9 against 7.5 ms at two).
+// Waves per SIMD the head kernel is compiled for: three (168 VGPRs, of which
+// 20 to 30 spill, with the transport fused in FP64 x 3 groups 85, smoothed 120)
+// are faster than two without spills (185 to 210 VGPRs).  us per step with the
+// fused transport, three / two waves: 96^3 x 3 490 / 540, FP64 612 / 634,
+// smoothed 550 / 571, without OTSA 560 / 600; 160^3 1,305 / 1,525, FP64 1,880 /
+// 1,948; 900 x 128 x 64 1,830 / 2,240.  With two passes after a separate
+// transport both take the same time.
 template <typename R, int M>
 constexpr int head_waves() { return 3; }
 

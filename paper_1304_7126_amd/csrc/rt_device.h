@@ -246,7 +246,7 @@ __device__ __forceinline__ void hll_axis(const R *__restrict__ tab, int nth, con
     const R a00 = (R(1) - wf) * (R(1) - wt), a10 = wf * (R(1) - wt), a01 = (R(1) - wf) * wt, a11 = wf * wt;
     if constexpr (sizeof(R) == 8) {
         // the FP64 device table holds lambda_max only: lambda_min(f, theta) =
-        // -lambda_max(f, pi - theta), whose nodes mirror (hll_device_table)
+        // -lambda_max(f, pi - theta), whose nodes mirror (upload_hll_table)
         const R *t0 = tab + p.i * nth, *t1 = t0 + nth;
         const int j = nth - 2 - k;
         lmax = a00 * t0[k] + a10 * t1[k] + a01 * t0[k + 1] + a11 * t1[k + 1];

@@ -155,8 +155,8 @@ struct ChemIO {
     // super-comoving state (a != 1): the arrays hold a^3 N and a^3 n_H, the
     // chemistry works on N and n_H
     double a3 = 1.0, ia3 = 1.0;
-    // attempts of each cell in the previous chemistry pass (capped at 255),
-    // read to order the tail and rewritten; null: not kept
+    // attempts of each cell in the previous chemistry pass (at most ATT_CAP),
+    // read to order the cells of this one and rewritten; null: not kept
     uint8_t *prev_att = nullptr;
 };
 

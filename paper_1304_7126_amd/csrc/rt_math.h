@@ -1,11 +1,12 @@
-// rt_math.h -- natural logarithms in FP64 for the App. E rate coefficients.
+// rt_math.h -- natural logarithms in FP64 for the adjoint's dual-number rates
+// and the angle of a flux to an axis for the FP64 transport.
 //
-// Every attempt of the thermochemistry (App. A) evaluates four ln T and
-// five ln(1 + u) of the Hui & Gnedin fits (App. E.2, E.3); the library
-// routines carry extended-precision intermediates that cost about twice the
-// instructions of the methods below, which stay within about 1.2 ulp (ln)
-// and 1.5 ulp (ln(1 + u)) of the exact values, far inside what the
-// subcycled solver needs.
+// The reverse chemistry linearises every substep through the Hui & Gnedin fits
+// of App. E.2 and E.3 themselves (the forward attempts read the table of
+// rt_rates.h); the library's logarithms carry extended-precision
+// intermediates that cost about twice the instructions of the methods below,
+// which stay within about 1.2 ulp (ln) and 1.5 ulp (ln(1 + u)) of the exact
+// values.
 //
 //   ln x: x = 2^e m with m in [sqrt(1/2), sqrt(2)); with f = m - 1 (exact)
 //   and s = f / (m + 1), ln m = 2 atanh(s) = 2s + 2s^3/3 + 2s^5/5 + ...,
@@ -14,9 +15,8 @@
 //   with z = s^2 and q(z) = 1/3 + z/5 + ... + z^9/21: the rounding of s then
 //   enters only through the small term s (...).  q is nested as
 //   (1/3)(1 + (3/5) z (1 + (5/7) z (1 + ...))): every addend is 1, an inline
-//   operand, and the ratios multiply z from scalar registers, where the
-//   compiler rematerialises them instead of holding ten FP64 constants in
-//   vector registers across the subcycling loop.  ln x = e ln 2 + ln m with
+//   operand, and the ratios multiply z from scalar registers instead of ten
+//   FP64 constants held in vector registers.  ln x = e ln 2 + ln m with
 //   ln 2 split into a 32-bit head and its remainder.
 //   ln(1 + u): w = 1 + u rounded, c = u - (w - 1) its rounding error (exact
 //   for u >= 0), ln(1 + u) = ln w + c / w to first order in c, with 1/w
@@ -71,8 +71,7 @@ __host__ __device__ __forceinline__ double rt_log(double x)
 }
 
 // ln(1 + u) for u >= 0 (the fits' (lambda/lambda_0)^q), with the library's
-// results for infinity and NaN; u < 0 is outside its domain (a further
-// select for it pushed the chemistry kernels past their register budget).
+// results for infinity and NaN; u < 0 is outside its domain.
 // The correction c / w = c 2^-e / m takes 1/m as 1 - f + f^2, within 5% on
 // the reduced range: c is below half an ulp of w, so that costs under 0.05
 // ulp.

@@ -27,7 +27,7 @@
 // of 256^3 cells with many hot ones was no faster than with the formulas
 // (4.95 against 4.84 ms per step).
 //
-// Measured with the persistent kernels that hold it (start / now): VALU
+// Measured with the persistent kernels that hold it (formulas / table): VALU
 // instructions of the chemistry at 256^3 x 3, 200 sources, 1.68e9 / 1.06e9
 // per launch; us per step 16^3 114 / 68, isothermal 32^3 103 / 62, 97 x 61 x
 // 45 603 / 387, 64^3 754 / 517, 128^3 FP64 1,536 / 1,121, 256^3 mixed 4,799 /

@@ -215,8 +215,14 @@ __device__ __forceinline__ void block_sum2(double a, double b, double &sa, doubl
 // alone (81.6 KB; lambda_min is its mirror image): in LDS it would have to
 // share the records' place with the fluxes, and the two more barriers per
 // plane cost more than the gathers (256^3 x 3: 2.68 against 2.51 ms; now
-// 2.58, with pairs in global memory, IEEE divisions and roots throughout and
-// the library's arccos 2.85).
+// 2.62, with pairs in global memory, IEEE divisions and roots throughout and
+// the library's arccos 2.84).
+// What bounds FP64 HLL (256^3 x 3, steps 1-20, 2.41 ms): not issue, 860 VALU
+// instructions per cell and group at 46% of the chip's rate, but 52% of the
+// wave cycles spent waiting.  The kernel takes all 256 VGPRs (20 spill, 84
+// bytes of scratch) and 96 KiB of LDS, so one workgroup of eight waves runs
+// per CU and all of them stop at both barriers of a plane; its tiles of two
+// rows read the state twice (3.3 GB for 1.6).
 constexpr int LTAB_CAP = 101 * 101 * 2;
 template <typename R, int FLUX, int NT, bool AHEAD>
 __global__ __launch_bounds__(NT) void k_transport_z(KGrid g, int H, int zc, R c, R kdx, const R *__restrict__ Nin,
