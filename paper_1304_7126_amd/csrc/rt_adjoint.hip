@@ -359,7 +359,7 @@ __global__ __launch_bounds__(256) void k_chem_record(const KChem *__restrict__ k
         xHII[i] = s.x;
         T[i] = Tout;
     } else {
-        fl |= 2u;
+        fl |= chem_refused(k, s);
     }
     if (fl) atomicOr(&st->flags, fl);
 }

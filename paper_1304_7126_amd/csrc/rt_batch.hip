@@ -244,7 +244,7 @@ __device__ __forceinline__ void head_chunk(const BoxDev &b, const KChem &k, uint
             done = false;
             for (int a = 0; a < K && !done; ++a) done = chem_attempt<CM>(k, rx, rt, cc, s, fl);
         } else {
-            fl |= 2u;
+            fl |= chem_refused(k, s);
         }
     }
     // Queue: long chains (by the substep they have come down to), warm gas and

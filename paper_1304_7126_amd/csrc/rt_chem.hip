@@ -114,7 +114,7 @@ __global__ __launch_bounds__(256, (head_waves<R, M>())) void k_head(KGrid g, con
             done = false;
             for (int a = 0; a < K && !done; ++a) done = chem_attempt<CM, V, false, false>(k, k.rates, nullptr, cc, s, fl);
         } else {
-            fl |= 2u;
+            fl |= chem_refused(k, s);
         }
     }
     if (FUSE && io.acct) block_acct(io.acct, av);
@@ -562,8 +562,8 @@ __global__ __launch_bounds__(CHEM_THREADS, CHEM_WAVES) void k_chem_all(const KCh
                         if (load(cell, true)) {
                             active = true;
                         } else {
-                            // a non-finite input: the cell is written back as loaded
-                            cfl = 2u;
+                            // the cell is written back as loaded
+                            cfl = chem_refused(k, s);
                             finish();
                         }
                     }

@@ -252,8 +252,8 @@ __host__ __device__ inline RateAt rate_at(double T)
     // an exponent below the table wraps to a large number: both ends are
     // clamped.  (A T that is not positive has an interval too, but none of its
     // rates is used: with T evolving the cooling's sqrt(T) is NaN and the
-    // attempt fails, an isothermal cell starts at the attempt cap (chem_init),
-    // and one that is not finite is refused there.)
+    // attempt fails; chem_init refuses an isothermal cell at T <= 0 and one
+    // whose T is not finite.)
     const uint32_t u = (hi - ((uint32_t)(1023 + RT_XE0) << 20)) >> 16;
     r.n = u < (uint32_t)RT_XNI ? u : (hi < 0x3FF00000u ? 0u : (uint32_t)RT_XNI - 1u);
     const uint64_t vb = ((uint64_t)((hi & 0x000FFFFFu) | 0x3FF00000u) << 32) | (uint32_t)b;

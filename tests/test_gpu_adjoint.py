@@ -301,3 +301,38 @@ def test_gradient_of_partly_filled_waves(n, srcs, iso):
         ref = cs.directional_derivative(p, s0, dt, w.steps, ijk, np.log(nd), np.log(st["nH"]), target.cpu().numpy(), vs, vc)
         got = float(g_src @ vs) if vs is not None else float(np.sum(g_nH * vc))
         assert abs(got - ref) <= 1e-8 * abs(ref) + 1e-12 * scale, (vs is not None, got, ref)
+
+
+def test_recorded_step_of_an_isothermal_cell_without_a_positive_temperature():
+    # rt_step and rt_step_record both leave it as it is, at the attempt cap
+    import ctypes
+    from paper_1304_7126_amd import RTContext, capi
+    from paper_1304_7126_amd.capi import lib
+    w = ri.grey_box(6, 3.3 * 6 / 64, 2, 1, seed=4, isothermal=True)
+    ijk, nd = ri.random_sources(w.n, w.n_sources, w.seed)
+    out = []
+    counts = None
+    for record in (False, True):
+        c = RTContext.for_workload(w, counters=True)
+        c.load_state(ri.initial_state(w))
+        c.T[1, 2, 3] = 0.0
+        c.T[4, 4, 4] = -50.0
+        c.set_sources(ijk, c.source_rates(nd))
+        c.reset_stats()
+        dt = c.courant_dt()
+        if record:
+            nc = counts.numel()
+            tot = int(counts.sum().item()) + nc
+            Na, Fa, tr = (torch.empty(n, dtype=torch.float64, device="cuda") for n in (nc, 3 * nc, 7 * tot))
+            off = torch.empty(lib().rt_tape_offsets_len(c._h), dtype=torch.int64, device="cuda")
+            t = capi.RtTape(Na.data_ptr(), Fa.data_ptr(), counts.data_ptr(), off.data_ptr(), tr.data_ptr(), tot)
+            capi.check(lib().rt_step_record(c._h, dt, ctypes.byref(t)), c._h)
+        else:
+            c.step(dt, 1)
+            counts = c.nacc.clone().contiguous()
+        torch.cuda.synchronize()
+        assert c.stats()["flags"] == 1
+        out.append((c.radiation()[0].clone(), c.radiation()[1].clone(), c.xHII.clone(), c.T.clone()))
+    for a, b in zip(*out):
+        assert torch.equal(a, b)
+    assert counts[1, 2, 3] == 0 and counts[4, 4, 4] == 0
